@@ -38,10 +38,45 @@ struct Mfma<double> {
   static __device__ __forceinline__ int row(int q4, int r) { return q4 + 4 * r; }
 };
 
+// Lane exchanges without LDS: a DPP move (the control codes are the wave64 row
+// operations quad_perm [1,0,3,2] = 0xB1 and [2,3,0,1] = 0x4E, row_half_mirror
+// = 0x141, row_mirror = 0x140, row_ror:8 = 0x128) and the value of one lane.
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_mov(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true));
+}
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+// Sum over the 64 lanes (all active), the same bits in every lane.  Register
+// latency: four DPP steps inside the rows of 16, then the four row sums
+// through the scalar unit; six LDS shuffles took about four times as long.
 template <typename T>
 __device__ __forceinline__ T wave_sum(T v) {
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  v += dpp_mov<0x140>(v);
+  return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
+}
+
+// Workgroup barrier for data exchanged through LDS alone: unlike
+// __syncthreads() it does not wait for the wave's global stores to complete
+// (about a microsecond in a step that has just stored a result).
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
 // Block-wide sum for blockDim.x == NT (multiple of 64); `red` holds NT/64

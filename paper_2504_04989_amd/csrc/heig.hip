@@ -5,13 +5,12 @@
 // vectors are C_f^H W diag(1/sigma).
 //
 // Four kernels, all batched over the Fourier slices:
-//  1. tridiag   one workgroup per slice: symmetrised sum of the split-K
-//               partials, then Householder reduction G = H T H^H,
-//               H = H_0 ... H_{m-2}, H_j = I - tau_j v_j v_j^H (complex
-//               reflectors with real beta, so T is real symmetric).  Each step
-//               touches the trailing matrix once: the rank-2 update of step s
-//               and the matrix-vector product of step s+1 share one pass.  The
-//               trailing matrix moves into LDS as soon as it fits.
+//  1. tridiag   symmetrised sum of the split-K partials, then Householder
+//               reduction G = H T H^H, H = H_0 ... H_{m-2},
+//               H_j = I - tau_j v_j v_j^H (complex reflectors with real beta,
+//               so T is real symmetric).  m <= TREG_MAX: one workgroup per
+//               slice with the triangle in registers (tridiag_reg.hip);
+//               larger m: one or several workgroups per slice, below.
 //  2. bisect    one wave per eigenvalue: 64-way multisection on Sturm counts
 //               of T for the k largest eigenvalues.
 //  3. invit     one wave per cluster of close eigenvalues: inverse iteration
@@ -22,417 +21,17 @@
 #include <algorithm>
 
 #include "common.h"
+#include "heig_common.h"
 #include "kernels.h"
 
 
 namespace tsvd {
 
-constexpr int TRI_PMAX = 8;  // workgroups per slice of the blocked tridiagonalisation, at most
-
-static inline size_t heig_per_slice(int m, int k) {
-  (void)k;
-  const size_t mp = (size_t)(m + 31) / 32 * 32;
-  // A (m x m), tau (m), d and e (m each), the partial products exchanged by the
-  // workgroups of a slice (2 x TRI_PMAX x mp) and their barrier counters
-  size_t b = (size_t)16 * m * m + (size_t)16 * m + (size_t)16 * m;
-  b = (b + 255) & ~(size_t)255;
-  b += (size_t)2 * TRI_PMAX * mp * 16 + 256;
-  return (b + 255) & ~(size_t)255;
-}
 size_t heig_scratch_bytes(int m, int k) { return heig_per_slice(m, k); }
 
-__device__ __forceinline__ cx<double> cmulc(cx<double> a, cx<double> b) {
-  return cx<double>{a.re * b.re - a.im * b.im, a.re * b.im + a.im * b.re};
-}
-// conj(a) * b
-__device__ __forceinline__ cx<double> cjmul(cx<double> a, cx<double> b) {
-  return cx<double>{a.re * b.re + a.im * b.im, a.re * b.im - a.im * b.re};
-}
-
-struct HeigView {
-  cx<double>* A;  // m x m working matrix (global)
-  cx<double>* tau;
-  double* d;
-  double* e;
-  cx<double>* ypg;  // 2 x TRI_PMAX x mp partial products of the slice's workgroups
-  unsigned* sync;   // barrier counter and abort flag of the slice's workgroups
-  double* fscale;   // partial sums of ||G||_F^2 (PREP_WG of them): the fixed-point scale of the symv sums
-};
-__device__ __forceinline__ HeigView heig_view(unsigned char* scratch, size_t per_slice, int f, int m) {
-  HeigView v;
-  unsigned char* base = scratch + (size_t)f * per_slice;
-  v.A = reinterpret_cast<cx<double>*>(base);
-  v.tau = v.A + (size_t)m * m;
-  v.d = reinterpret_cast<double*>(v.tau + m);
-  v.e = v.d + m;
-  const size_t off = (((size_t)16 * m * m + (size_t)32 * m) + 255) & ~(size_t)255;
-  v.ypg = reinterpret_cast<cx<double>*>(base + off);
-  const size_t mp = (size_t)(m + 31) / 32 * 32;
-  v.sync = reinterpret_cast<unsigned*>(base + off + (size_t)2 * TRI_PMAX * mp * 16);
-  v.fscale = reinterpret_cast<double*>(v.sync + 2);
-  return v;
-}
-
 // ---------------------------------------------------------------------------
-// 1. Householder tridiagonalisation
-// ---------------------------------------------------------------------------
-// View of the working matrix: element (r, c) at p[(r - off) * ld + (c - off)].
-// One instantiation per memory space keeps LDS accesses as LDS instructions.
-struct MatView {
-  cx<double>* p;
-  int ld, off;
-  __device__ __forceinline__ cx<double>* at(int r, int c) const { return p + (int64_t)(r - off) * ld + (c - off); }
-};
-
-struct TriShared {
-  double* red;  // 2 * (NT / 64) doubles
-  cx<double>* tau;
-  cx<double>* scale;
-  int* skip;
-  cx<double>* ppart;  // TRI_G x m partial sums of p
-};
-
-#ifndef TSVD_TRI_NT
-#define TSVD_TRI_NT 512
-#endif
-#ifndef TSVD_TRI_NB
-#define TSVD_TRI_NB 8
-#endif
-constexpr int TRI_NT = TSVD_TRI_NT;  // threads per tridiagonalisation workgroup
-constexpr int TRI_G = 8;     // at most this many thread groups share one column
-
-// Block-wide sum of a complex value (one reduction for both parts).
-__device__ __forceinline__ cx<double> block_sum_cx(cx<double> v, double* red) {
-  v.re = wave_sum(v.re);
-  v.im = wave_sum(v.im);
-  const int w = threadIdx.x >> 6;
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) {
-    red[2 * w] = v.re;
-    red[2 * w + 1] = v.im;
-  }
-  __syncthreads();
-  cx<double> r{0, 0};
-#pragma unroll
-  for (int i = 0; i < TRI_NT / 64; ++i) {
-    r.re += red[2 * i];
-    r.im += red[2 * i + 1];
-  }
-  return r;
-}
-
-// Reflector of step s from row s (the conjugate of column s below the
-// diagonal), given s2 = the squared norm of its entries after the first:
-// writes v (length m - s - 1, v[0] = 1) to `dst` and to row s of the global
-// matrix, and records d[s], e[s], tau[s].
-__device__ __forceinline__ void tri_reflector_from(const MatView& B, int s, int m, double s2, cx<double>* dst,
-                                                   const HeigView& hv, const TriShared& sh) {
-  const int tid = threadIdx.x;
-  const int L = m - s - 1;
-  const cx<double>* row = B.at(s, s + 1);
-  if (tid == 0) {
-    hv.d[s] = B.at(s, s)->re;
-    const double ar = row[0].re, ai = -row[0].im;
-    if (s2 == 0.0 && ai == 0.0) {
-      *sh.skip = 1;
-      hv.e[s] = ar;
-      *sh.tau = cx<double>{0, 0};
-    } else {
-      *sh.skip = 0;
-      const double beta = -copysign(sqrt(ar * ar + ai * ai + s2), ar);
-      *sh.tau = cx<double>{(beta - ar) / beta, -ai / beta};
-      const double dr = ar - beta, di = ai;
-      const double den = dr * dr + di * di;
-      *sh.scale = cx<double>{dr / den, -di / den};
-      hv.e[s] = beta;
-    }
-    hv.tau[s] = *sh.tau;
-  }
-  __syncthreads();
-  const bool skip = *sh.skip != 0;
-  const cx<double> scale = *sh.scale;
-  cx<double>* grow = hv.A + (int64_t)s * m + (s + 1);
-  for (int i = tid; i < L; i += TRI_NT) {
-    cx<double> v;
-    if (i == 0) {
-      v = cx<double>{1.0, 0.0};
-    } else if (skip) {
-      v = cx<double>{0.0, 0.0};
-    } else {
-      const cx<double> a = row[i];
-      v = cmulc(cx<double>{a.re, -a.im}, scale);
-    }
-    dst[i] = v;
-    grow[i] = v;
-  }
-  __syncthreads();
-}
-
-__device__ __forceinline__ void tri_reflector(const MatView& B, int s, int m, cx<double>* dst, const HeigView& hv,
-                                              const TriShared& sh) {
-  const int L = m - s - 1;
-  const cx<double>* row = B.at(s, s + 1);
-  double s2 = 0;
-  for (int i = 1 + threadIdx.x; i < L; i += TRI_NT) {
-    const cx<double> a = row[i];
-    s2 += a.re * a.re + a.im * a.im;
-  }
-  s2 = block_sum_cx(cx<double>{s2, 0.0}, sh.red).re;
-  tri_reflector_from(B, s, m, s2, dst, hv, sh);
-}
-
-// (a) w_s = p_s - (tau_s / 2) (p_s^H v_s) v_s, in place over p_s.
-__device__ __forceinline__ void tri_w(int L, const cx<double>* vb, cx<double>* wb, const TriShared& sh) {
-  const int tid = threadIdx.x;
-  const cx<double> tau = *sh.tau;
-  cx<double> acc{0, 0};
-  for (int i = tid; i < L; i += TRI_NT) {
-    const cx<double> t = cjmul(wb[i], vb[i]);
-    acc.re += t.re;
-    acc.im += t.im;
-  }
-  acc = block_sum_cx(acc, sh.red);
-  const cx<double> a2 = cmulc(cx<double>{-0.5 * tau.re, -0.5 * tau.im}, acc);
-  const bool zero = (tau.re == 0.0 && tau.im == 0.0);
-  for (int i = tid; i < L; i += TRI_NT) {
-    if (zero) {
-      wb[i] = cx<double>{0, 0};
-    } else {
-      const cx<double> t = cmulc(a2, vb[i]);
-      wb[i].re += t.re;
-      wb[i].im += t.im;
-    }
-  }
-  __syncthreads();
-}
-
-// Last step (trailing size 1): d[m-1].
-__device__ __forceinline__ void tri_last(const MatView& B, int m, const cx<double>* vb, const cx<double>* wb,
-                                         const HeigView& hv) {
-  if (threadIdx.x == 0) {
-    const cx<double> v = vb[0], w = wb[0];
-    hv.d[m - 1] = B.at(m - 1, m - 1)->re - 2.0 * (v.re * w.re + v.im * w.im);
-    hv.e[m - 1] = 0.0;
-  }
-}
-
-// (c) row s+1 of the step-s update (and the norm for the next reflector),
-// (d) the reflector of step s+1, (e) the rest of the step-s update of
-// A[s+2:, s+2:] fused with p_{s+1} = tau_{s+1} A' v_{s+1}; the rows of each
-// column are split over up to TRI_G thread groups.
-__device__ __forceinline__ void tri_cde(const MatView& B, int s, int m, const cx<double>* vb, const cx<double>* wb,
-                                        cx<double>* vn, cx<double>* pn, const HeigView& hv, const TriShared& sh) {
-  const int tid = threadIdx.x;
-  const int L = m - s - 1;
-  double s2 = 0;
-  {
-    cx<double>* row = B.at(s + 1, s + 1);
-    const cx<double> v0 = vb[0], w0 = wb[0];
-    for (int c = tid; c < L; c += TRI_NT) {
-      const cx<double> vc = vb[c], wc = wb[c];
-      cx<double> a = row[c];
-      a.re -= (v0.re * wc.re + v0.im * wc.im) + (w0.re * vc.re + w0.im * vc.im);
-      a.im -= (v0.im * wc.re - v0.re * wc.im) + (w0.im * vc.re - w0.re * vc.im);
-      row[c] = a;
-      if (c >= 2) s2 += a.re * a.re + a.im * a.im;  // entries of row s+1 after its first off-diagonal
-    }
-  }
-  s2 = block_sum_cx(cx<double>{s2, 0.0}, sh.red).re;
-  tri_reflector_from(B, s + 1, m, s2, vn, hv, sh);
-  const int Ln = L - 1;
-  if (Ln <= 0) return;
-  const cx<double> taun = *sh.tau;
-  int G = TRI_NT / Ln;
-  if (G > TRI_G) G = TRI_G;
-  if (G < 1) G = 1;
-  constexpr int NB = TSVD_TRI_NB;  // rows per batch; the next batch is loaded while this one is updated
-  const int64_t ld = B.ld;
-  for (int t = tid; t < G * Ln || (G == 1 && t < Ln); t += TRI_NT) {
-    const int g = G > 1 ? t / Ln : 0;
-    const int cc = G > 1 ? t - g * Ln : t;
-    const int c = s + 2 + cc;
-    const cx<double> vc = vb[cc + 1], wc = wb[cc + 1];
-    double ar = 0, ai = 0;
-    cx<double>* colp = B.at(s + 2, c);
-    auto upd = [&](cx<double> x, int r) {
-      const cx<double> vr = vb[r + 1], wr = wb[r + 1];
-      x.re -= (vr.re * wc.re + vr.im * wc.im) + (wr.re * vc.re + wr.im * vc.im);
-      x.im -= (vr.im * wc.re - vr.re * wc.im) + (wr.im * vc.re - wr.re * vc.im);
-      colp[(int64_t)r * ld] = x;
-      const cx<double> tt = cjmul(x, vn[r]);
-      ar += tt.re;
-      ai += tt.im;
-    };
-    // rows g, g + G, g + 2G, ... of this column
-    const int nrows = (Ln - g + G - 1) / G;
-    const int nfull = nrows / NB;
-    int q = 0;
-    if (nfull > 0) {
-      cx<double> a[NB];
-#pragma unroll
-      for (int u = 0; u < NB; ++u) a[u] = colp[(int64_t)(g + u * G) * ld];
-      for (int bt = 0; bt < nfull - 1; ++bt, q += NB) {
-        cx<double> an[NB];
-#pragma unroll
-        for (int u = 0; u < NB; ++u) an[u] = colp[(int64_t)(g + (q + NB + u) * G) * ld];
-#pragma unroll
-        for (int u = 0; u < NB; ++u) upd(a[u], g + (q + u) * G);
-#pragma unroll
-        for (int u = 0; u < NB; ++u) a[u] = an[u];
-      }
-#pragma unroll
-      for (int u = 0; u < NB; ++u) upd(a[u], g + (q + u) * G);
-      q += NB;
-    }
-    for (; q < nrows; ++q) upd(colp[(int64_t)(g + q * G) * ld], g + q * G);
-    if (G > 1)
-      sh.ppart[g * m + cc] = cx<double>{ar, ai};
-    else
-      pn[cc] = cmulc(taun, cx<double>{ar, ai});
-  }
-  __syncthreads();
-  if (G > 1) {
-    for (int cc = tid; cc < Ln; cc += TRI_NT) {
-      cx<double> acc{0, 0};
-      for (int g = 0; g < G; ++g) {
-        acc.re += sh.ppart[g * m + cc].re;
-        acc.im += sh.ppart[g * m + cc].im;
-      }
-      pn[cc] = cmulc(taun, acc);
-    }
-    __syncthreads();
-  }
-}
-
-// A = Hermitian part of the sum of the nsum partials (or the Hermitian
-// extension of their upper triangle), written to the slice's working matrix.
-template <int NT>
-__device__ __forceinline__ void tri_load_hermitian(const cx<double>* __restrict__ G, int nsum, int64_t part_stride,
-                                                   int m, int upper_only, cx<double>* A) {
-  const int tid = threadIdx.x;
-  // sum of the partials (partial index outermost: independent loads in flight)
-  const int mm = m * m;
-  for (int s = 0; s < nsum; ++s) {
-    const cx<double>* Gs = G + s * part_stride;
-#pragma unroll 8
-    for (int t = tid; t < mm; t += NT) {
-      const cx<double> g = Gs[t];
-      if (s == 0) {
-        A[t] = g;
-      } else {
-        cx<double> a = A[t];
-        a.re += g.re;
-        a.im += g.im;
-        A[t] = a;
-      }
-    }
-  }
-  __syncthreads();
-  // Hermitian average (upper triangle from the lower one, diagonal real), or
-  // the Hermitian extension of the upper triangle when only that is valid
-  for (int t = tid; t < mm; t += NT) {
-    const int i = t / m, c = t - (t / m) * m;
-    if (c > i) continue;
-    const cx<double> g = A[t], h = A[(int64_t)c * m + i];
-    const cx<double> lo = upper_only ? cx<double>{h.re, i == c ? 0.0 : -h.im}
-                                     : cx<double>{0.5 * (g.re + h.re), i == c ? 0.0 : 0.5 * (g.im - h.im)};
-    A[t] = lo;
-    A[(int64_t)c * m + i] = cx<double>{lo.re, -lo.im};
-  }
-  __syncthreads();
-}
-
-__global__ __launch_bounds__(TRI_NT) void heig_tridiag_kernel(const cx<double>* __restrict__ Gpart, int nsum,
-                                                           int64_t part_stride, int m, unsigned char* scratch,
-                                                           size_t per_slice, int Lsw, int upper_only) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  cx<double>* vbuf0 = reinterpret_cast<cx<double>*>(smem);
-  cx<double>* vbuf1 = vbuf0 + m;
-  cx<double>* wbuf0 = vbuf1 + m;
-  cx<double>* wbuf1 = wbuf0 + m;
-  cx<double>* ppart = wbuf1 + m;          // TRI_G x m partial sums
-  cx<double>* Tl = ppart + TRI_G * m;     // LDS copy of the trailing matrix
-  __shared__ double red[2 * (TRI_NT / 64)];
-  __shared__ cx<double> s_tau, s_scale;
-  __shared__ int s_skip;
-  const TriShared sh{red, &s_tau, &s_scale, &s_skip, ppart};
-  const int tid = threadIdx.x;
-  const int f = blockIdx.x;
-  const HeigView hv = heig_view(scratch, per_slice, f, m);
-  cx<double>* A = hv.A;
-  const cx<double>* G = Gpart + (int64_t)f * m * m;
-
-  tri_load_hermitian<TRI_NT>(G, nsum, part_stride, m, upper_only, A);
-  if (m == 1) {
-    if (tid == 0) {
-      hv.d[0] = A[0].re;
-      hv.e[0] = 0.0;
-      hv.tau[0] = cx<double>{0, 0};
-    }
-    return;
-  }
-  const MatView Bg{A, m, 0};
-  int cur = 0;  // which of the two vector buffers holds v_s / p_s
-  auto vb = [&](int which) { return which ? vbuf1 : vbuf0; };
-  auto wb = [&](int which) { return which ? wbuf1 : wbuf0; };
-
-  // step 0: reflector and p_0 = tau_0 A[1:, 1:] v_0 (global)
-  tri_reflector(Bg, 0, m, vbuf0, hv, sh);
-  {
-    const int L = m - 1;
-    const cx<double> tau = s_tau;
-    for (int c = tid; c < L; c += TRI_NT) {
-      double ar = 0, ai = 0;
-#pragma unroll 4
-      for (int r = 0; r < L; ++r) {
-        const cx<double> t = cjmul(*Bg.at(r + 1, c + 1), vbuf0[r]);
-        ar += t.re;
-        ai += t.im;
-      }
-      wbuf0[c] = cmulc(tau, cx<double>{ar, ai});
-    }
-    __syncthreads();
-  }
-  // global phase
-  int s = 0;
-  bool done = false;
-  for (; s < m - 1; ++s) {
-    const int L = m - s - 1;
-    tri_w(L, vb(cur), wb(cur), sh);
-    if (s == m - 2) {
-      tri_last(Bg, m, vb(cur), wb(cur), hv);
-      done = true;
-      break;
-    }
-    if (L <= Lsw) break;
-    tri_cde(Bg, s, m, vb(cur), wb(cur), vb(cur ^ 1), wb(cur ^ 1), hv, sh);
-    cur ^= 1;
-  }
-  if (done) return;
-  // LDS phase: the trailing matrix A[s+1:, s+1:] (w_s already formed)
-  const int L0 = m - s - 1;
-  for (int r = tid / 32; r < L0; r += TRI_NT / 32)
-    for (int c = tid % 32; c < L0; c += 32) Tl[r * L0 + c] = A[(int64_t)(s + 1 + r) * m + (s + 1 + c)];
-  __syncthreads();
-  const MatView Bl{Tl, L0, s + 1};
-  tri_cde(Bl, s, m, vb(cur), wb(cur), vb(cur ^ 1), wb(cur ^ 1), hv, sh);
-  cur ^= 1;
-  for (++s; s < m - 1; ++s) {
-    const int L = m - s - 1;
-    tri_w(L, vb(cur), wb(cur), sh);
-    if (s == m - 2) {
-      tri_last(Bl, m, vb(cur), wb(cur), hv);
-      break;
-    }
-    tri_cde(Bl, s, m, vb(cur), wb(cur), vb(cur ^ 1), wb(cur ^ 1), hv, sh);
-    cur ^= 1;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// 1b. Blocked tridiagonalisation for larger m (panels of NB reflectors).
-// The same reflectors as the unblocked kernel, but within a panel the trailing
-// matrix is only read: step i forms y = A_tr v_i from the matrix as it stood
+// 1. Blocked tridiagonalisation for m > TREG_MAX (panels of NB reflectors).
+// Within a panel the trailing matrix is only read: step i forms y = A_tr v_i from the matrix as it stood
 // at the start of the panel and corrects it with the panel's earlier
 // reflectors, y -= V (W^H v) + W (V^H v); the panel's 2 NB rank-one terms
 // A -= V W^H + W V^H are applied once at its end.  Only the lower triangle is
@@ -442,8 +41,7 @@ __global__ __launch_bounds__(TRI_NT) void heig_tridiag_kernel(const cx<double>* 
 // 4 (lane / 8) + q, columns lane % 8 + 8 p); row and column sums are
 // finished with three lane exchanges each and added into y in LDS.  The
 // panel's V and W stay in LDS.  The trailing matrix is read about once per
-// step at half size, against a read and a write of the full matrix per step in
-// the unblocked form.  The waves' additions into y land in an order that
+// step at half size.  The waves' additions into y land in an order that
 // depends on timing, so they are made in 64-bit fixed point (integer addition
 // is associative): a contribution x is added as rint(x 2^62 / S) with S a power
 // of two >= m ||G||_F.  Every partial sum of a row of the trailing matrix times
@@ -453,21 +51,6 @@ __global__ __launch_bounds__(TRI_NT) void heig_tridiag_kernel(const cx<double>* 
 // ---------------------------------------------------------------------------
 constexpr int T2_NT = 512;
 constexpr int T2_W = T2_NT / 64;
-
-__device__ __forceinline__ cx<double> cadd(cx<double> a, cx<double> b) { return cx<double>{a.re + b.re, a.im + b.im}; }
-__device__ __forceinline__ cx<double> shfl_xor_cx(cx<double> v, int mask) {
-  return cx<double>{__shfl_xor(v.re, mask, 64), __shfl_xor(v.im, mask, 64)};
-}
-// a += x * y
-__device__ __forceinline__ void cfma(cx<double>& a, cx<double> x, cx<double> y) {
-  a.re = fma(x.re, y.re, fma(-x.im, y.im, a.re));
-  a.im = fma(x.re, y.im, fma(x.im, y.re, a.im));
-}
-// a += conj(x) * y
-__device__ __forceinline__ void cfmac(cx<double>& a, cx<double> x, cx<double> y) {
-  a.re = fma(x.re, y.re, fma(x.im, y.im, a.re));
-  a.im = fma(x.re, y.im, fma(-x.im, y.re, a.im));
-}
 
 template <int NW = T2_W, bool LEAD_SYNC = true>
 __device__ __forceinline__ cx<double> block_sum2(cx<double> v, double* red) {
@@ -502,15 +85,6 @@ __device__ __forceinline__ cx<double> reduce4(const cx<double> (&y)[4], int lane
   const cx<double> kk = h1 ? t1 : t0, ss = h1 ? t0 : t1;
   const cx<double> u = cadd(kk, shfl_xor_cx(ss, X1));
   return cadd(u, shfl_xor_cx(u, X2));
-}
-
-// tile t of the lower triangle of tiles with first tile row / column J0 (row-major order)
-__device__ __forceinline__ void tri_tile(int t, int J0, int& I, int& J) {
-  int a = (int)((sqrt(8.0 * t + 1.0) - 1.0) * 0.5);
-  while ((a + 1) * (a + 2) / 2 <= t) ++a;
-  while (a * (a + 1) / 2 > t) --a;
-  J = t - a * (a + 1) / 2 + J0;
-  I = a + J0;
 }
 
 // The lane's 4 x 4 block: rows r0 + q, columns c0 + 8 p (eight lanes of a row
@@ -1852,8 +1426,6 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
   static bool attr_set = false;
   if (!attr_set) {
     // dynamic LDS limits, leaving room for each kernel's static LDS
-    (void)hipFuncSetAttribute((const void*)heig_tridiag_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              152 * 1024);
     (void)hipFuncSetAttribute((const void*)heig_tri2_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               152 * 1024);
     (void)hipFuncSetAttribute((const void*)heig_tri2_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1865,21 +1437,19 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
   }
   const size_t per = heig_per_slice(m, k);
   unsigned char* sc = (unsigned char*)scratch;
-  // 1. tridiagonalisation: vectors (4 m) + trailing matrix in LDS (Lsw^2)
   const size_t lds_total = 150 * 1024;
-  const size_t vec_bytes = (size_t)(4 + TRI_G) * m * sizeof(cx<double>);
-  int Lsw = 0;
-  if (lds_total > vec_bytes) {
-    Lsw = (int)sqrt((double)(lds_total - vec_bytes) / sizeof(cx<double>));
-    if (Lsw > m - 1) Lsw = m - 1;
-  }
-  const size_t sm1 = vec_bytes + (size_t)Lsw * Lsw * sizeof(cx<double>);
   hipError_t e = hipSuccess;
-  // blocked form when the matrix spans a few tiles and its panel fits in LDS
+  // 1. tridiagonalisation.  Up to TREG_MAX rows the triangle fits one
+  // workgroup's registers: 1.6 to 4.4 us per step, against 3.5 to 10 us for the
+  // streaming form at the same sizes and about 8.5 us with several workgroups
+  // per slice (an exchange through memory in every step).
   const int MP = (m + 31) / 32 * 32;
   auto sm2 = [&](int nb) { return ((size_t)(2 * nb + 3) * MP + 2 * nb) * sizeof(cx<double>); };
-  const bool blocked = m >= 64 && m <= 2 * T2_NT + 1;
-  if ((stages & HEIG_TRIDIAG) && blocked && sm2(4) <= lds_total) {
+  if ((stages & HEIG_TRIDIAG) && m <= TREG_MAX) {
+    if ((e = heig_tridiag_reg((const cx<double>*)Gpart, nsum, part_stride, m, batch, sc, per, upper_only ? 1 : 0, s)) !=
+        hipSuccess)
+      return e;
+  } else if (stages & HEIG_TRIDIAG) {
     const int nb = sm2(8) <= lds_total ? 8 : 4;
     const size_t sm = sm2(nb);
     const void* fn = nb == 8 ? (const void*)heig_tri2_kernel<8> : (const void*)heig_tri2_kernel<4>;
@@ -1937,10 +1507,6 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
         hipLaunchKernelGGL(heig_tri2_kernel<4>, dim3(batch), dim3(T2_NT), sm, s, G, nsum_a, ps, m_a, mp_a, sc_a, per_a,
                            up, 1, info_a);
     }
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-  } else if (stages & HEIG_TRIDIAG) {
-    hipLaunchKernelGGL(heig_tridiag_kernel, dim3(batch), dim3(TRI_NT), sm1, s, (const cx<double>*)Gpart, nsum,
-                       part_stride, m, sc, per, Lsw, upper_only ? 1 : 0);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // 2. eigenvalues: 4 waves (eigenvalues) per workgroup
