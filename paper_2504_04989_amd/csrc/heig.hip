@@ -11,14 +11,15 @@
 //               so T is real symmetric).  m <= TREG_MAX: one workgroup per
 //               slice with the triangle in registers (tridiag_reg.hip);
 //               larger m: one or several workgroups per slice, below.
-//  2. bisect    one wave per eigenvalue: 64-way multisection on Sturm counts
-//               of T for the k largest eigenvalues.
-//  3. invit     one wave per cluster of close eigenvalues: inverse iteration
-//               on the pivoted LU of T - lambda I (in LDS), members of a
-//               cluster re-orthogonalised against each other.
+//  2. bisect    multisection on Sturm counts of T for the k largest
+//               eigenvalues, 8, 16 or 64 lanes per eigenvalue.
+//  3. invit     one lane per eigenvector: inverse iteration on the pivoted LU
+//               of T - lambda I; then the members of a cluster of close
+//               eigenvalues are orthogonalised against each other.
 //  4. backxf    W = H Z, several workgroups per slice, each owning 8 columns
 //               of W in LDS.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.h"
 #include "heig_common.h"
@@ -903,18 +904,21 @@ __global__ __launch_bounds__(RES_NT, 1) void heig_trires_kernel(const cx<double>
 // ---------------------------------------------------------------------------
 // 2. eigenvalues by multisection (one wave per eigenvalue)
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int sturm_count(const double* d, const double* e2, int m, double x, double pivmin) {
+// Number of eigenvalues of T below x; de holds (d_i, e_{i-1}^2).
+__device__ __forceinline__ int sturm_count(const double2* de, int m, double x, double pivmin) {
   int cnt = 0;
-  double q = d[0] - x;
+  double q = de[0].x - x;
   if (fabs(q) < pivmin) q = -pivmin;
   cnt += q < 0;
+#pragma unroll 4
   for (int i = 1; i < m; ++i) {
     // e2 / q with the hardware reciprocal refined by one Newton step (a
     // relative perturbation of e2 at rounding level: the count stays the
     // exact count of a nearby tridiagonal matrix)
+    const double2 t = de[i];
     double r = __builtin_amdgcn_rcp(q);
     r = r * fma(-q, r, 2.0);
-    q = (d[i] - x) - e2[i - 1] * r;
+    q = (t.x - x) - t.y * r;
     if (fabs(q) < pivmin) q = -pivmin;
     cnt += q < 0;
   }
@@ -952,42 +956,58 @@ __device__ void tri_bounds(const double* d, const double* e, int m, double* gl, 
   *gu = hi + 2.0 * eps * tn * m + 2.0 * (*pivmin);
 }
 
+// Multisection with L lanes per eigenvalue, 64 / L eigenvalues per wave: each
+// round places L points in the interval and keeps the one section that holds
+// the eigenvalue.  Bound: the vector issue of m steps per round and wave when
+// there are several waves per SIMD, the latency of that chain otherwise.  More
+// lanes per eigenvalue mean fewer rounds (9 to 10 for L = 64, 13 for 16, 17 for
+// 8) of more waves.
+template <int L>
 __global__ __launch_bounds__(256) void heig_bisect_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
                                                           double* __restrict__ lambda_out, int* info) {
   extern __shared__ __align__(16) unsigned char smem[];
-  double* d = reinterpret_cast<double*>(smem);
+  double2* de = reinterpret_cast<double2*>(smem);
+  double* d = reinterpret_cast<double*>(de + m);
   double* e = d + m;
-  double* e2 = e + m;
   const int f = blockIdx.x;
   HeigView hv = heig_view(scratch, per_slice, f, m);
   for (int i = threadIdx.x; i < m; i += blockDim.x) {
     d[i] = hv.d[i];
     e[i] = hv.e[i];
-    e2[i] = hv.e[i] * hv.e[i];
+    const double ep = i > 0 ? hv.e[i - 1] : 0.0;
+    de[i] = double2{hv.d[i], ep * ep};
   }
   __syncthreads();
+  constexpr int E = 64 / L;  // eigenvalues per wave
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int t = blockIdx.y * (blockDim.x >> 6) + wave;
-  if (t >= k) return;
+  const int t0 = (blockIdx.y * (blockDim.x >> 6) + wave) * E;
+  if (t0 >= k) return;
+  const int g = lane / L, l = lane % L;
+  const int t = min(t0 + g, k - 1);  // (a group past k repeats the last eigenvalue and does not store it)
   double lo, hi, pivmin, tnorm;
   tri_bounds(d, e, m, &lo, &hi, &pivmin, &tnorm);
   const int idx = m - 1 - t;
   const double eps = 2.220446049250313e-16;
-  for (int it = 0; it < 64; ++it) {
-    if (hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin) break;
-    const double x = lo + (hi - lo) * (double)(lane + 1) / 65.0;
-    const int cnt = sturm_count(d, e2, m, x, pivmin);
-    const unsigned long long above = __ballot(cnt > idx);  // lanes whose point lies above lambda_idx
-    const int p = above ? __ffsll((long long)above) - 1 : 64;  // first such lane
-    const double xp = __shfl(x, p < 64 ? p : 63, 64);
-    const double xm = __shfl(x, p > 0 ? p - 1 : 0, 64);
+  bool done = false;
+  for (int it = 0; it < 96; ++it) {
+    // (the last term only ends the search for an exact zero)
+    if (hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin + 1e-30 * tnorm) done = true;
+    if (__ballot(!done) == 0ull) break;
+    const double x = lo + (hi - lo) * (double)(l + 1) / (double)(L + 1);
+    const int cnt = sturm_count(de, m, x, pivmin);
+    unsigned long long above = __ballot(cnt > idx) >> (g * L);  // lanes whose point lies above lambda_idx
+    if (L < 64) above &= (1ull << (L & 63)) - 1;
+    const int p = above ? __ffsll((long long)above) - 1 : L;  // first such lane of the group
+    const double xp = __shfl(x, g * L + (p < L ? p : L - 1), 64);
+    const double xm = __shfl(x, g * L + (p > 0 ? p - 1 : 0), 64);
     const double nlo = p > 0 ? xm : lo;
-    const double nhi = p < 64 ? xp : hi;
-    if (nlo == lo && nhi == hi) break;
+    const double nhi = p < L ? xp : hi;
+    if (done) continue;
+    if (nlo == lo && nhi == hi) done = true;
     lo = nlo;
     hi = nhi;
   }
-  if (lane == 0) {
+  if (l == 0 && t0 + g < k) {
     const double lv = 0.5 * (lo + hi);
     lambda_out[(int64_t)f * k + t] = lv;
     if (!isfinite(lv)) atomicAdd(&info[INFO_NONFINITE], 1);
@@ -995,30 +1015,8 @@ __global__ __launch_bounds__(256) void heig_bisect_kernel(int m, int k, unsigned
 }
 
 // ---------------------------------------------------------------------------
-// 3. eigenvectors of T by inverse iteration (one wave per cluster)
+// 3. eigenvectors of T by inverse iteration (one lane per eigenvector)
 // ---------------------------------------------------------------------------
-// Order LDS traffic between the lanes of one wave (the wave runs in lockstep;
-// this keeps the compiler from moving LDS accesses across the point).
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-  __builtin_amdgcn_wave_barrier();
-}
-
-// Waves (eigenvectors) per workgroup of the inverse iteration.  The LU
-// factors and the iterate live in registers (NCH 64-entry chunks per lane);
-// LDS holds T (2 m doubles) and one m-vector per wave for the residual.
-constexpr int INVIT_NW = 4;
-
-// Value of v held by lane j (j uniform across the wave): two v_readlane_b32.
-// The dependent chains of the inverse iteration walk through a 64-entry chunk
-// that the lanes fetched from LDS in parallel, at register latency.
-__device__ __forceinline__ double lane_get(double v, int j) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u & 0xffffffffull), j);
-  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(u >> 32), j);
-  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
-}
-
 __device__ __forceinline__ double hash_uniform(uint32_t a, uint32_t b) {
   uint32_t h = a * 0x9E3779B1u ^ (b + 0x7F4A7C15u) * 0x85EBCA77u;
   h ^= h >> 15;
@@ -1029,211 +1027,241 @@ __device__ __forceinline__ double hash_uniform(uint32_t a, uint32_t b) {
   return (double)h * (2.0 / 4294967296.0) - 1.0;
 }
 
-template <int NCH>
-__global__ __launch_bounds__(256) void heig_invit_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
-                                                         const double* __restrict__ lambda,
-                                                         cx<double>* __restrict__ Wout, int* info,
-                                                         double vfloor_rel) {
+// Eigenvalues closer than INVIT_ORTOL ||T|| form a cluster, whose vectors are
+// orthogonalised against each other afterwards (heig_cluster_kernel); those
+// further apart carry a contamination of at most about eps / 1e-9 = 2e-7 by
+// their neighbours.
+constexpr double INVIT_ORTOL = 1e-9;
+constexpr int INVIT_B = 8;
+
+// One eigenvector per lane, nl of them per one-wave workgroup: the pivoted LU of
+// T - lambda I and the solves are chains of m dependent steps, and the chains
+// of all lanes cost what one did when a wave walked one.  Bound: the latency of
+// those chains (about 4 m steps).  The reciprocal pivots, multipliers and
+// iterate of the lanes are in LDS (24 m nl bytes; fetched from memory instead,
+// the chains ran at a third of the speed); the entry right of the pivot follows
+// from T, the multipliers and the row-swap bits.  T is scaled by a power of two
+// to ||T|| in [1, 2).
+__global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, unsigned char* scratch, size_t per_slice,
+                                                        const double* __restrict__ lambda, cx<double>* Wout, int* info,
+                                                        double vfloor_rel) {
   extern __shared__ __align__(16) unsigned char smem[];
-  double* d = reinterpret_cast<double*>(smem);
-  double* e = d + m;
-  const int f = blockIdx.x;
-  const int nw = blockDim.x >> 6;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  double* zs = e + m + (size_t)wave * m;  // this wave's iterate, for the residual
+  // Rows go in batches of B: a batch's operands are read from LDS together, so
+  // the chain waits for LDS once per batch.  The rows are padded to whole batches
+  // by uncoupled ones, so that no row takes a branch.
+  constexpr int B = INVIT_B;
+  const int mp = (m + B - 1) / B * B;
+  double* d = reinterpret_cast<double*>(smem);                // mp + 1
+  double* e = d + mp + 1;                                     // mp + 1
+  double* R = e + mp + 1;                                     // mp x nl: 1 / pivot
+  double* Mu = R + mp * nl;                                   // mp x nl: multipliers
+  double* Z = Mu + mp * nl;                                   // mp x nl: the iterate
+  unsigned char* swaps = reinterpret_cast<unsigned char*>(Z + mp * nl);  // mp / B x 64: swap bits of a batch
+  const int f = blockIdx.x, lane = threadIdx.x;
   HeigView hv = heig_view(scratch, per_slice, f, m);
-  for (int i = threadIdx.x; i < m; i += blockDim.x) {
-    d[i] = hv.d[i];
-    e[i] = hv.e[i];
+  for (int i = lane; i <= mp; i += 64) {
+    d[i] = i < m ? hv.d[i] : 4.0;
+    e[i] = i + 1 < m ? hv.e[i] : 0.0;
   }
   __syncthreads();
-  const int t0 = blockIdx.y * nw + wave;
-  if (t0 >= k) return;
-  const double* lam = lambda + (int64_t)f * k;
-  cx<double>* W = Wout + (int64_t)f * m * k;
   double gl, gu, pivmin, tnorm;
   tri_bounds(d, e, m, &gl, &gu, &pivmin, &tnorm);
-  const double eps = 2.220446049250313e-16;
-  // Eigenvalues closer than ortol form a cluster whose vectors are computed
-  // in sequence and re-orthogonalised against each other; vectors of
-  // eigenvalues further apart are computed independently (in parallel), with
-  // a contamination of about eps * ||T|| / gap <= 2e-7 by their neighbours.
-  const double ortol = 1e-9 * tnorm;
-  // eigenvalues at or below vfloor_rel * lambda_0 (when vfloor_rel > 0) get a
-  // zero vector and are not computed: a caller that discards them saves the
-  // inverse iterations of a large cluster near zero
-  const bool use_floor = vfloor_rel > 0.0;
-  const double vfloor = vfloor_rel * lam[0];
-  if (use_floor && !(lam[t0] > vfloor)) {
-    for (int i = lane; i < m; i += 64) W[(int64_t)i * k + t0] = cx<double>{0.0, 0.0};
+  const int t = blockIdx.y * nl + lane;
+  const double* lam = lambda + (int64_t)f * k;
+  cx<double>* W = Wout + (int64_t)f * m * k + t;
+  const bool act = lane < nl && t < k;
+  int ex = 0;
+  (void)frexp(tnorm, &ex);
+  const double up = isfinite(tnorm) && tnorm > 0.0 ? ldexp(1.0, 1 - ex) : 1.0;
+  __syncthreads();
+  for (int i = lane; i < m; i += 64) {
+    d[i] *= up;  // (the padding rows keep 4: off any eigenvalue)
+    e[i] *= up;
+  }
+  __syncthreads();
+  if (!act) return;  // (one wave, no barrier below)
+  if (tnorm == 0.0) {  // the zero matrix: unit vectors
+    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{i == t ? 1.0 : 0.0, 0.0};
     return;
   }
-  if (t0 > 0 && lam[t0 - 1] - lam[t0] < ortol) return;  // not the head of its cluster
-  int t1 = t0 + 1;
-  while (t1 < k && lam[t1 - 1] - lam[t1] < ortol && !(use_floor && !(lam[t1] > vfloor))) ++t1;
-  const double tinyp = eps * fmax(tnorm, 1e-300);
-  for (int t = t0; t < t1; ++t) {
-    const double lv = lam[t];
-    // pivoted LU of T - lambda I; entry 64 c + lane of the factors (reciprocal
-    // pivot, the two entries right of it, multiplier, row swap) stays in this
-    // lane's registers, chunk c.  The recurrence runs, uniform, in every lane.
-    double r0[NCH], r1[NCH], r2[NCH], rmu[NCH], rsw[NCH], Z[NCH];
-    double pc = d[0] - lv, qc = (m > 1) ? e[0] : 0.0, rc = 0.0;
+  const double lv = lam[t] * up;
+  const double eps = 2.220446049250313e-16;
+  R += lane;
+  Mu += lane;
+  Z += lane;
+  swaps += lane;
+  // LU with row interchanges; pivots are kept at or above eps in modulus
+  {
+    double pc = d[0] - lv, qc = e[0];
+    for (int i0 = 0; i0 < mp; i0 += B) {
+      double dn[B], eb[B + 1];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      r0[c] = 1.0;
-      r1[c] = r2[c] = rmu[c] = rsw[c] = 0.0;
-      const int base = 64 * c;
-      if (base < m - 1) {
-        const int i = base + lane;
-        const int cnt = min(64, m - 1 - base);
-        const double ei_l = i < m - 1 ? e[i] : 0.0;
-        const double an_l = i < m - 1 ? d[i + 1] - lv : 0.0;
-        const double en_l = i + 1 < m - 1 ? e[i + 1] : 0.0;
-        double o0 = 1.0, o1 = 0.0, o2 = 0.0, om = 0.0, os = 0.0;
-        for (int j = 0; j < cnt; ++j) {
-          const double ei = lane_get(ei_l, j);
-          const double an = lane_get(an_l, j);
-          const double en = lane_get(en_l, j);
-          double s0, s1, s2, sm, ss;
-          if (fabs(pc) >= fabs(ei)) {
-            double piv = pc;
-            if (fabs(piv) < tinyp) piv = copysign(tinyp, piv == 0.0 ? 1.0 : piv);
-            const double mu = ei / piv;
-            s0 = piv;
-            s1 = qc;
-            s2 = rc;
-            sm = mu;
-            ss = 0.0;
-            pc = an - mu * qc;
-            qc = en - mu * rc;
-            rc = 0.0;
-          } else {
-            const double mu = pc / ei;
-            s0 = ei;
-            s1 = an;
-            s2 = en;
-            sm = mu;
-            ss = 1.0;
-            const double npc = qc - mu * an;
-            const double nqc = rc - mu * en;
-            pc = npc;
-            qc = nqc;
-            rc = 0.0;
-          }
-          if (lane == j) {
-            o0 = s0;
-            o1 = s1;
-            o2 = s2;
-            om = sm;
-            os = ss;
-          }
-        }
-        if (lane < cnt) {
-          r0[c] = 1.0 / o0;  // the solves multiply by the reciprocal pivots
-          r1[c] = o1;
-          r2[c] = o2;
-          rmu[c] = om;
-          rsw[c] = os;
-        }
+      for (int u = 0; u < B; ++u) {
+        dn[u] = d[i0 + u + 1] - lv;
+        eb[u] = e[i0 + u];
+      }
+      eb[B] = e[i0 + B];
+      unsigned bits = 0;
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const double ei = eb[u], an = dn[u], en = eb[u + 1];
+        const bool sw = fabs(pc) < fabs(ei);
+        double den = sw ? ei : pc;
+        den = fabs(den) < eps ? copysign(eps, den) : den;
+        double r = __builtin_amdgcn_rcp(den);
+        r = fma(fma(-den, r, 1.0), r, r);
+        r = fma(fma(-den, r, 1.0), r, r);
+        const double mu = (sw ? pc : ei) * r;
+        pc = fma(-mu, sw ? an : qc, sw ? qc : an);
+        qc = sw ? -mu * en : en;
+        R[(i0 + u) * nl] = r;
+        Mu[(i0 + u) * nl] = mu;
+        bits |= (unsigned)sw << u;
+      }
+      swaps[(i0 / B) * 64] = (unsigned char)bits;
+    }
+  }
+  // Back substitution: the entries right of the pivot are (d_{i+1} - lambda,
+  // e_{i+1}) in a swapped row, else e_i, or -mu_{i-1} e_i behind a swapped row.
+  // FIRST: of a random right-hand side (zero in the padding rows).  Returns ||z||^2.
+  auto back = [&](auto first) {
+    constexpr bool FIRST = decltype(first)::value;
+    double z1 = 0.0, z2 = 0.0, nrm = 0.0;
+    for (int i0 = mp - B; i0 >= 0; i0 -= B) {
+      const unsigned bits = swaps[(i0 / B) * 64];
+      const unsigned low = i0 > 0 ? swaps[(i0 / B - 1) * 64] >> (B - 1) : 0;  // row i0 - 1 swapped
+      double cb[B], mb[B], rb[B], db[B], eb[B + 1];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const int i = i0 + u;
+        if (FIRST)
+          cb[u] = i < m ? hash_uniform((uint32_t)t, (uint32_t)i) : 0.0;
+        else
+          cb[u] = Z[i * nl];
+        mb[u] = Mu[(u > 0 ? i - 1 : max(i - 1, 0)) * nl];
+        rb[u] = R[i * nl];
+        db[u] = d[i + 1] - lv;
+        eb[u] = e[i];
+      }
+      eb[B] = e[i0 + B];
+#pragma unroll
+      for (int u = B - 1; u >= 0; --u) {
+        const bool sw = (bits >> u) & 1u, swp = (u > 0 ? bits >> (u > 0 ? u - 1 : 0) : low) & 1u;
+        const double r1 = sw ? db[u] : (swp ? -mb[u] * eb[u] : eb[u]);
+        const double r2 = sw ? eb[u + 1] : 0.0;
+        const double v = fma(-r1, z1, fma(-r2, z2, cb[u])) * rb[u];
+        Z[(i0 + u) * nl] = v;
+        nrm = fma(v, v, nrm);
+        z2 = z1;
+        z1 = v;
       }
     }
-    if (fabs(pc) < tinyp) pc = copysign(tinyp, pc == 0.0 ? 1.0 : pc);
+    return nrm;
+  };
+  double nrm = back(std::true_type{});
+  double scale = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0, res = 1.0;
+  for (int it = 1; it < 4; ++it) {
+    // forward elimination of the normalised iterate
+    double zc = Z[0] * scale;
+    for (int i0 = 0; i0 < mp; i0 += B) {
+      const unsigned bits = swaps[(i0 / B) * 64];
+      double zb[B], mb[B];
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      if (64 * c + lane == m - 1) {
-        r0[c] = 1.0 / pc;
-        r1[c] = r2[c] = 0.0;
-      }
-      const int i = 64 * c + lane;
-      Z[c] = i < m ? hash_uniform((uint32_t)t, (uint32_t)i) : 0.0;
-    }
-    for (int it = 0; it < 4; ++it) {
-      // forward elimination with the row swaps and multipliers, then back
-      // substitution, uniform in every lane over the chunks; z[i + 1] of
-      // step i is the next lane's entry (or lane 0 of the next chunk)
-      double zc = lane_get(Z[0], 0);
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) {
-        const int base = 64 * c;
-        if (base < m - 1) {
-          const int cnt = min(64, m - 1 - base);
-          const double znext = c + 1 < NCH ? lane_get(Z[c + 1 < NCH ? c + 1 : c], 0) : 0.0;
-          double out = 0.0;
-          for (int j = 0; j < cnt; ++j) {
-            double zn = j < 63 ? lane_get(Z[c], j + 1) : znext;
-            if (lane_get(rsw[c], j) != 0.0) {
-              const double tmp = zc;
-              zc = zn;
-              zn = tmp;
-            }
-            if (lane == j) out = zc;
-            zc = zn - lane_get(rmu[c], j) * zc;
-          }
-          if (lane < cnt) Z[c] = out;
-        }
+      for (int u = 0; u < B; ++u) {
+        zb[u] = Z[(u < B - 1 ? i0 + u + 1 : min(i0 + B, mp - 1)) * nl] * scale;
+        mb[u] = Mu[(i0 + u) * nl];
       }
 #pragma unroll
-      for (int c = 0; c < NCH; ++c)
-        if (64 * c + lane == m - 1) Z[c] = zc;
-      double z1 = 0.0, z2 = 0.0;
-#pragma unroll
-      for (int c = NCH - 1; c >= 0; --c) {
-        const int base = 64 * c;
-        if (base < m) {
-          const int cnt = min(64, m - base);
-          double out = 0.0;
-          for (int j = cnt - 1; j >= 0; --j) {
-            const double v = (lane_get(Z[c], j) - lane_get(r1[c], j) * z1 - lane_get(r2[c], j) * z2) *
-                             lane_get(r0[c], j);
-            if (lane == j) out = v;
-            z2 = z1;
-            z1 = v;
-          }
-          if (lane < cnt) Z[c] = out;
-        }
+      for (int u = 0; u < B; ++u) {
+        const bool sw = (bits >> u) & 1u;
+        const double x = sw ? zb[u] : zc, y = sw ? zc : zb[u];
+        Z[(i0 + u) * nl] = x;  // (the last row neither swaps nor feeds another)
+        zc = fma(-mb[u], x, y);
       }
-      // re-orthogonalise against the earlier members of the cluster
-      for (int t2 = t0; t2 < t; ++t2) {
-        double cc = 0;
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const int i = 64 * c + lane;
-          if (i < m) cc += Z[c] * W[(int64_t)i * k + t2].re;
+    }
+    nrm = back(std::false_type{});
+    // the right-hand side had norm 1 (from the second solve on), so the
+    // normalised iterate's residual is 1 / ||z||
+    scale = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
+    res = nrm > 0.0 && isfinite(nrm) ? scale : 1.0;
+    if (__ballot(!(res <= 16.0 * m * eps)) == 0ull) break;
+  }
+  // eigenvalues at or below vfloor_rel * lambda_0 (when vfloor_rel > 0) get a zero vector
+  const bool floor_out = vfloor_rel > 0.0 && !(lam[t] > vfloor_rel * lam[0]);
+  if (!floor_out && !(res <= 1e3 * m * eps)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
+#pragma unroll 4
+  for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{floor_out ? 0.0 : Z[i * nl] * scale, 0.0};
+}
+
+// Orthogonalisation inside the clusters of close eigenvalues, one workgroup per
+// slice: classical Gram-Schmidt, twice, in the order of the eigenvalues.  The
+// members come out of independent random starts, so they span the cluster's
+// invariant subspace, and a combination of members stays within the cluster's
+// width (below 1e-9 ||T|| per gap, weighted by the members' contamination eps /
+// gap) of an eigenvector.  A slice without clusters returns at once.
+__global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
+                                                           const double* __restrict__ lambda, cx<double>* Wout,
+                                                           int* info, double vfloor_rel, int lds_cols) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  double* lam = reinterpret_cast<double*>(smem);  // k
+  double* coef = lam + k;                         // k
+  double* cur = coef + k;                         // m: the vector being orthogonalised
+  double* buf = cur + m;                          // lds_cols x m: the cluster's earlier members
+  __shared__ double red[4];
+  const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+  HeigView hv = heig_view(scratch, per_slice, f, m);
+  cx<double>* W = Wout + (int64_t)f * m * k;
+  for (int t = tid; t < k; t += 256) lam[t] = lambda[(int64_t)f * k + t];
+  double tn = 0;
+  for (int i = lane; i < m; i += 64) {
+    const double r = (i + 1 < m ? fabs(hv.e[i]) : 0.0) + (i > 0 ? fabs(hv.e[i - 1]) : 0.0);
+    tn = fmax(tn, fabs(hv.d[i]) + r);
+  }
+  tn = wave_max(tn);
+  __syncthreads();
+  const double ortol = INVIT_ORTOL * tn;
+  const double vfloor = vfloor_rel > 0.0 ? vfloor_rel * lam[0] : -1e300;
+  bool any = false;
+  for (int t = 1 + tid; t < k; t += 256) any |= lam[t - 1] - lam[t] < ortol;
+  if (!__syncthreads_or(any)) return;
+  for (int t0 = 0; t0 + 1 < k;) {
+    int t1 = t0 + 1;
+    while (t1 < k && lam[t1 - 1] - lam[t1] < ortol && (!(vfloor_rel > 0.0) || lam[t1] > vfloor)) ++t1;
+    const int n = t1 - t0;
+    const bool in_lds = n <= lds_cols;
+    auto member = [&](int c, int i) { return in_lds ? buf[(size_t)c * m + i] : W[(int64_t)i * k + t0 + c].re; };
+    for (int j = 0; n > 1 && j < n; ++j) {
+      for (int i = tid; i < m; i += 256) cur[i] = W[(int64_t)i * k + t0 + j].re;
+      __syncthreads();
+      for (int pass = 0; pass < 2 && j > 0; ++pass) {
+        for (int c = wv; c < j; c += 4) {
+          double s = 0;
+          for (int i = lane; i < m; i += 64) s = fma(member(c, i), cur[i], s);
+          s = wave_sum(s);
+          if (lane == 0) coef[c] = s;
         }
-        cc = wave_sum(cc);
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) {
-          const int i = 64 * c + lane;
-          if (i < m) Z[c] -= cc * W[(int64_t)i * k + t2].re;
+        __syncthreads();
+        for (int i = tid; i < m; i += 256) {
+          double s = cur[i];
+          for (int c = 0; c < j; ++c) s = fma(-coef[c], member(c, i), s);
+          cur[i] = s;
         }
+        __syncthreads();
       }
-      double nrm = 0;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) nrm += Z[c] * Z[c];
-      nrm = wave_sum(nrm);
-      nrm = nrm > 0 ? 1.0 / sqrt(nrm) : 0.0;
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) Z[c] *= nrm;
+      double s = 0;
+      for (int i = tid; i < m; i += 256) s = fma(cur[i], cur[i], s);
+      s = block_sum<256>(s, red);
+      // (a member inside the span of the earlier ones would be left without digits)
+      if (tid == 0 && !(s > 1e-14)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
+      const double sc = s > 0 ? 1.0 / sqrt(s) : 0.0;
+      for (int i = tid; i < m; i += 256) {
+        const double x = cur[i] * sc;
+        if (in_lds) buf[(size_t)j * m + i] = x;
+        if (j > 0) W[(int64_t)i * k + t0 + j].re = x;
+      }
+      __syncthreads();
     }
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int i = 64 * c + lane;
-      if (i < m) zs[i] = Z[c];
-    }
-    wave_sync();
-    double res = 0;
-    for (int i = lane; i < m; i += 64) {
-      double y = (d[i] - lv) * zs[i];
-      if (i > 0) y += e[i - 1] * zs[i - 1];
-      if (i + 1 < m) y += e[i] * zs[i + 1];
-      res = fmax(res, fabs(y));
-    }
-    res = wave_max(res);
-    if (lane == 0 && !(res <= 1e3 * m * eps * fmax(tnorm, 1e-300))) atomicAdd(&info[INFO_EIG_NOCONV], 1);
-    for (int i = lane; i < m; i += 64) W[(int64_t)i * k + t] = cx<double>{zs[i], 0.0};
-    wave_sync();
-    __threadfence();
+    t0 = t1;
   }
 }
 
@@ -1509,28 +1537,62 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // 2. eigenvalues: 4 waves (eigenvalues) per workgroup
+  // 2. eigenvalues: 4 waves per workgroup.  With at most one wave per SIMD
+  // (1024 of them) 64 lanes per eigenvalue take the fewest rounds; past that the
+  // waves share issue slots and fewer lanes per eigenvalue cost less.
   if (stages & HEIG_BISECT) {
-    hipLaunchKernelGGL(heig_bisect_kernel, dim3(batch, (k + 3) / 4), dim3(256), (size_t)3 * m * sizeof(double), s,
-                       m, k, sc, per, lambda, info);
+    const size_t sm = (size_t)4 * m * sizeof(double);
+    const int64_t n = (int64_t)batch * k;
+    auto go = [&](auto kernel, int per_wave) {
+      hipLaunchKernelGGL(kernel, dim3(batch, (k + 4 * per_wave - 1) / (4 * per_wave)), dim3(256), sm, s, m, k, sc, per,
+                         lambda, info);
+    };
+    if (n <= 1024)
+      go(heig_bisect_kernel<64>, 1);
+    else if (n <= 4096)
+      go(heig_bisect_kernel<16>, 4);
+    else
+      go(heig_bisect_kernel<8>, 8);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  // 3. eigenvectors: LU factors and iterates in registers (NCH chunks of 64
-  // entries per lane), T and one m-vector per wave in LDS
+  // 3. eigenvectors: g workgroups per slice with nl = ceil(k / g) lanes each.
+  // The time is a chain of about 4 m steps per round of workgroups whatever nl
+  // is, so g is the smallest count with the fewest rounds over the CUs (an LDS
+  // of 160 KB holds one workgroup or several); then the clusters.
   if (stages & HEIG_INVIT) {
-    const int nw = INVIT_NW;
-    const size_t sm3 = (size_t)(2 + nw) * m * sizeof(double);
-    const dim3 g3(batch, (k + nw - 1) / nw), b3(64 * nw);
-    if (m <= 128)
-      hipLaunchKernelGGL(heig_invit_kernel<2>, g3, b3, sm3, s, m, k, sc, per, lambda, (cx<double>*)W, info, vfloor_rel);
-    else if (m <= 256)
-      hipLaunchKernelGGL(heig_invit_kernel<4>, g3, b3, sm3, s, m, k, sc, per, lambda, (cx<double>*)W, info, vfloor_rel);
-    else if (m <= 512)
-      hipLaunchKernelGGL(heig_invit_kernel<8>, g3, b3, sm3, s, m, k, sc, per, lambda, (cx<double>*)W, info, vfloor_rel);
-    else
-      hipLaunchKernelGGL(heig_invit_kernel<16>, g3, b3, sm3, s, m, k, sc, per, lambda, (cx<double>*)W, info,
-                         vfloor_rel);
+    const size_t lds_cu = 160 * 1024;
+    auto lds_of = [&](int nl) {
+      const size_t mp = (size_t)(m + INVIT_B - 1) / INVIT_B * INVIT_B;
+      return 16 * (mp + 1) + 24 * mp * nl + mp / INVIT_B * 64;
+    };
+    int best = 0;
+    int64_t best_rounds = 0;
+    for (int g = (k + 63) / 64; g <= k; ++g) {
+      const size_t lds = lds_of((k + g - 1) / g);
+      if (lds > lds_cu) continue;
+      const int64_t slots = 256 * (int64_t)std::min<size_t>(lds_cu / lds, 8);
+      const int64_t rounds = ((int64_t)batch * g + slots - 1) / slots;
+      if (best == 0 || rounds < best_rounds) {
+        best = g;
+        best_rounds = rounds;
+      }
+      if (best_rounds == 1) break;
+    }
+    const int nl = (k + best - 1) / best;
+    const size_t sm3 = lds_of(nl);
+    if ((e = hipFuncSetAttribute((const void*)heig_invit_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                 (int)lds_cu)) != hipSuccess)
+      return e;
+    hipLaunchKernelGGL(heig_invit_kernel, dim3(batch, (k + nl - 1) / nl), dim3(64), sm3, s, m, k, nl, sc, per, lambda,
+                       (cx<double>*)W, info, vfloor_rel);
     if ((e = hipGetLastError()) != hipSuccess) return e;
+    if (k > 1) {
+      const size_t base = (size_t)(2 * k + m) * sizeof(double);
+      const int cols = (int)std::min<size_t>(k, (60 * 1024 - base) / (m * sizeof(double)));
+      hipLaunchKernelGGL(heig_cluster_kernel, dim3(batch), dim3(256), base + (size_t)cols * m * sizeof(double), s, m, k,
+                         sc, per, lambda, (cx<double>*)W, info, vfloor_rel, cols);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
   }
   // 4. back-transformation
   const size_t sm4 = ((size_t)m * 8 + m) * sizeof(cx<double>);

@@ -945,12 +945,13 @@ int svd_and_lift(const Ctx& c, void* U, void* S, void* V) {
     // T1 = T (I - W_J W_J^H), and takes the top eigenpairs of T1^H T1, whose
     // absolute error scales with the much smaller norm of the rest; they are
     // projected off W_J once more and fill the columns from J on.
+    // (no vectors are formed below half that level: tail_split keeps none of them)
     double* lam1 = c.at<double>(p.o_lam1);
     double* W1 = c.at<double>(p.o_w1);
     for (const auto& sc : stage_cls) {
       Timed tm_(sc[1], c.s);
       HIPCHK(heig_topk(part, nsum_g, p.F * p.m * p.m, (int)p.m, (int)p.k, (int)p.F, lam1, W1, c.at(p.o_heig),
-                       c.info(), c.s, sc[0], false));
+                       c.info(), c.s, sc[0], false, 0.5e-9));
     }
     int* J = c.at<int>(p.o_split);
     void* W1m = c.at(p.o_w1m);

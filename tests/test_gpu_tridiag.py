@@ -31,3 +31,18 @@ def test_tile_edges_vs_lapack(m, batch):
         assert np.max(np.linalg.norm(R, axis=0)) <= 1e-12 * m * ref[0]
         assert np.max(np.abs(W[f].conj().T @ W[f] - np.eye(k))) <= 1e-10
 
+
+def test_identity_and_diagonal_reflectors():
+    """Columns whose reflector is the identity: a diagonal matrix, a matrix
+    with a zero trailing block, and the zero matrix."""
+    m, k = 40, 6
+    G = np.zeros((3, m, m), dtype=np.complex128)
+    G[0] = np.diag(np.arange(m, 0, -1.0))
+    G[1, :20, :20] = _gram(1, 20, seed=1, decay=1.0)[0]
+    lam, W, info = api.diag_heig(torch.tensor(G, device="cuda"), k)
+    assert info["nonfinite"] == 0
+    lam, W = host(lam), host(W)
+    for f in range(3):
+        ref = np.linalg.eigvalsh(G[f])[::-1][:k]
+        assert np.max(np.abs(lam[f] - ref)) <= 1e-13 * m * max(ref[0], 1e-300)
+        assert np.max(np.abs(G[f] @ W[f] - W[f] * lam[f])) <= 1e-12 * m * max(ref[0], 1e-300)
