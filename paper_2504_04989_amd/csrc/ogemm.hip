@@ -45,7 +45,8 @@ struct OArgs {
   int nsplit, kchunk;
   int nbig, nthin, total, per;
   int xvec;
-  int upper;  // TN: skip tiles strictly below the diagonal of a square product
+  int upper;  // TN: skip tiles strictly below the diagonal
+  int mb;     // upper-triangle kernel: 128-row blocks of the output
   int triu;   // NN: B is upper triangular (zeros below the diagonal, stored)
 };
 
@@ -280,14 +281,20 @@ __global__ __launch_bounds__(256, 2) void ogemm_kernel(const OArgs a) {
   }
 }
 
-// TN product of a square block with itself, upper triangle only, N <= 120
-// (the block Grams): with one 64-row tile per wave the upper-triangle skip
-// leaves the waves unequal (14, 12, 10, 8 thin tiles for N = 110, and a second
-// row tile of mostly padding).  Here wave w owns the row groups w and 7 - w
-// (16 rows each), 2 tt - 14 <= 16 thin tiles in all, and one workgroup per
-// slice and split covers the whole triangle.  Accumulator slot s holds thin
+// TN product of which only the upper triangle (trapezoid, M <= N) is read,
+// N > 64: the Grams and R = Q^H A.  The output is cut into 128-column chunks.
+// A workgroup on the diagonal block of a chunk gives wave w the row groups w
+// and 7 - w (16 rows each): 2 tt - 14 <= 18 thin tiles in all, the same for
+// every wave, where one 64-row tile per wave would leave them unequal (16, 14,
+// 12, 10 thin tiles) behind the step's barrier.  The rows above the diagonal
+// block are 64-row tiles, one row group and tt <= 16 thin tiles per wave, in
+// the same launch and with the same registers.  Accumulator slot s holds thin
 // tile s of group w when 2 w <= s < tt, else the next tile of group 7 - w.
-__global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
+// Bound by the FP64 matrix rate: 128 x 128 x 4096 over 33 slices 302 us with
+// 64-row tiles (MFMA busy 42%, half the product skipped for no gain) against
+// @G@ here; 256 x 256 x 4096: 1210 (64-column chunks) against @H@.
+__global__ __launch_bounds__(256, 2) void ogemm_tn_upper_kernel(const OArgs a) {
+  constexpr int SLOTS = 18;
   constexpr int TT = 16;
   constexpr int ROWS = TT * 16;
   constexpr int BUF = ROWS * OSTRIDE;
@@ -298,19 +305,31 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
   const int id = blockIdx.x;
   const int t = (id & 7) * a.per + (id >> 3);
   if (t >= a.total) return;
-  const int sp = t % a.nsplit;
-  const int f = t / a.nsplit;
+  // block of this workgroup within the slice: chunk by chunk, the row tiles
+  // above the diagonal block, then that block
+  int u = t % a.nbig, tc = 0;
+  const int mt = (a.M + 63) / 64;
+  while (u >= min(2 * tc, mt) + (tc < a.mb ? 1 : 0)) {
+    u -= min(2 * tc, mt) + (tc < a.mb ? 1 : 0);
+    ++tc;
+  }
+  const bool diag = u == 2 * tc;
+  const int sp = (t / a.nbig) % a.nsplit;
+  const int f = t / a.nbig / a.nsplit;
+  const int n0 = NCH * tc, m0 = 64 * u;
   const int kb = sp * a.kchunk;
   const int ke = min(a.K, kb + a.kchunk);
-  const int nc = a.N;
+  const int nc = min(NCH, a.N - n0);
   const int tt = (2 * nc + 15) / 16;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // uniform: slot choices branch on scalars
   const int q4 = lane >> 4, r16 = lane & 15;
   const float* Xf = a.X + (int64_t)f * a.strideX;
-  const int ga = wave, gb = 7 - wave;
-  const int cola = 16 * ga + r16, colb = 16 * gb + r16;
+  // off the diagonal every slot below tt belongs to the first group and the
+  // second one has none
+  const int ga = diag ? wave : 0, gb = diag ? 7 - wave : 8;
+  const int cola = m0 + 16 * wave + r16, colb = diag ? m0 + 16 * gb + r16 : cola;
   const bool oka = cola < a.M, okb = colb < a.M;
   const int cla = oka ? cola : a.M - 1, clb = okb ? colb : a.M - 1;
 
@@ -333,15 +352,15 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
     }
   };
   // full steps: every load issued, unconditionally, so that the next step's
-  // loads stay in flight across this step's MFMAs.  Padding columns nn >= N
-  // read column N - 1 instead of zeros: a thin row only reaches the output
+  // loads stay in flight across this step's MFMAs.  Padding columns read
+  // the chunk's last one instead of zeros: a thin row only reaches the output
   // rows it forms itself, and rows n >= N are never stored.
   // held as loaded (FP32 pairs), widened when stored to LDS
   auto load_thin_full = [&](int k0, float2 (&x)[TEL]) {
 #pragma unroll
     for (int e = 0; e < TEL; ++e) {
       const int idx = tid + e * 256;
-      const int kk = idx % OKSTEP, nn = min(idx / OKSTEP, nc - 1);
+      const int kk = idx % OKSTEP, nn = n0 + min(idx / OKSTEP, nc - 1);
       x[e] = reinterpret_cast<const float2*>(a.B)[(int64_t)f * a.strideB + (int64_t)(k0 + kk) * a.ldb + nn];
     }
   };
@@ -351,7 +370,7 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
       const int idx = tid + e * 256;
       const int kk = idx % OKSTEP, nn = idx / OKSTEP;
       float2 v = make_float2(0.f, 0.f);
-      if (k0 + kk < ke && nn < nc) v = reinterpret_cast<const float2*>(a.B)[(int64_t)f * a.strideB + (int64_t)(k0 + kk) * a.ldb + nn];
+      if (k0 + kk < ke && nn < nc) v = reinterpret_cast<const float2*>(a.B)[(int64_t)f * a.strideB + (int64_t)(k0 + kk) * a.ldb + n0 + nn];
       x[e] = v;
     }
   };
@@ -378,16 +397,16 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
     return 2 * gb + idx;
   };
 
-  f64x4 acc[TT];
+  f64x4 acc[SLOTS];
 #pragma unroll
-  for (int i = 0; i < TT; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
+  for (int i = 0; i < SLOTS; ++i) acc[i] = f64x4{0.0, 0.0, 0.0, 0.0};
   auto compute = [&](const double* buf, const float (&va)[4], const float (&vb)[4]) {
     // register vectors, selected whole (a select between two arrays would
     // become a select between their addresses, i.e. private memory)
     const f64x4 dav = {(double)va[0], (double)va[1], (double)va[2], (double)va[3]};
     const f64x4 dbv = {(double)vb[0], (double)vb[1], (double)vb[2], (double)vb[3]};
 #pragma unroll
-    for (int s = 0; s < TT; ++s) {
+    for (int s = 0; s < SLOTS; ++s) {
       bool useb;
       const int tile = slot_tile(s, useb);
       if (tile < tt) {
@@ -442,7 +461,7 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
   // columns (same row pair): one exchange, then whole complex numbers
   const bool odd = q4 & 1;
 #pragma unroll
-  for (int s = 0; s < TT; ++s) {
+  for (int s = 0; s < SLOTS; ++s) {
     bool useb;
     const int tile = slot_tile(s, useb);
     if (tile >= tt) continue;
@@ -456,7 +475,7 @@ __global__ __launch_bounds__(256, 2) void ogemm_tn_pair_kernel(const OArgs a) {
       const int rr = odd ? 2 + h : h;
       const double re = odd ? other[rr] : acc[s][rr];
       const double im = odd ? acc[s][rr] : other[rr];
-      const int n = 8 * tile + (q4 >> 1) + 2 * rr;
+      const int n = n0 + 8 * tile + (q4 >> 1) + 2 * rr;
       if (n >= a.N) continue;
       double2* out = static_cast<double2*>(a.C) + (((int64_t)sp * a.batch + f) * a.M * a.N + (int64_t)col * a.N + n);
       *out = make_double2(re, im);
@@ -514,9 +533,9 @@ int othin_tiles(int N) {
 }
 
 // TN thin tiles: an upper-triangle product wider than one 128-column chunk
-// (the Gram of C, m = 440) takes 64-column chunks, so the chunks that straddle
-// the diagonal waste less (28 of 49 tiles computed at m = 440, against 19 of
-// 28 twice as wide): 3.55 -> 3.22 ms for that Gram at 4096 x 4096 x 64.
+// takes 64-column chunks, so the chunks that straddle the diagonal waste less
+// (28 of 49 tiles computed at m = 440, against 19 of 28 twice as wide):
+// 3.55 -> 3.22 ms for the Gram of C at 4096 x 4096 x 64.
 int tn_thin_tiles(int N, bool upper) { return (upper && N > 128) ? 8 : othin_tiles(N); }
 
 void fill_grid(OArgs& a, int TT) {
@@ -545,76 +564,63 @@ int ogemm_slots() {
   return slots;
 }
 
-// Workgroups of a TN launch that do work (the others skip tiles strictly
-// below the diagonal of a square upper-only product).
+// Workgroups per slice and split of the upper-triangle kernel.
+int tn_upper_blocks(int M, int N) {
+  const int mt = (M + 63) / 64, mb = (M + 127) / 128;
+  int n = 0;
+  for (int tc = 0; tc < (N + 127) / 128; ++tc) n += std::min(2 * tc, mt) + (tc < mb ? 1 : 0);
+  return n;
+}
+
+// Workgroups of the general kernel that do work (the others skip tiles
+// strictly below the diagonal of an upper-only product).
 int64_t tn_live_tiles(int M, int N, int batch, bool upper) {
-  const int TT = tn_thin_tiles(N, upper && M == N), NCH = 8 * TT;
+  const int NCH = 8 * tn_thin_tiles(N, upper);
   const int nthin = (N + NCH - 1) / NCH, nbig = (M + 63) / 64;
   int64_t live = 0;
   for (int bt = 0; bt < nbig; ++bt)
-    for (int tc = 0; tc < nthin; ++tc) live += (upper && M == N && bt * 64 > tc * NCH + NCH - 1) ? 0 : 1;
+    for (int tc = 0; tc < nthin; ++tc) live += (upper && bt * 64 > tc * NCH + NCH - 1) ? 0 : 1;
   return live * batch;
 }
 
-}  // namespace
-
-// Split of the contraction for a TN product: the smallest makespan in K steps
-// over the device's workgroup slots, rounds x (steps per split + a fixed
-// per-workgroup cost), plus the reduction of the partials.
-int ogemm_tn_split(int M, int K, int N, int batch, bool upper) {
-  const int64_t live = tn_live_tiles(M, N, batch, upper);
+// Split of the contraction of a TN product of wgs workgroups: the smallest
+// makespan in K steps over the device's workgroup slots, rounds x (steps per
+// split + a fixed per-workgroup cost), plus the reduction of the partials.
+int tn_split(int64_t wgs, int K, int most, double* cost_out = nullptr) {
   const int64_t slots = ogemm_slots();
   int best = 1;
   double bcost = 1e300;
-  for (int ns = 1; ns <= 16; ++ns) {
+  for (int ns = 1; ns <= most; ++ns) {
     int kc = (K + ns - 1) / ns;
     kc = (kc + OKSTEP - 1) / OKSTEP * OKSTEP;
     if (ns > 1 && kc < 16 * OKSTEP) break;  // keep at least 16 steps per split
     const int nsx = (K + kc - 1) / kc;
-    const int64_t rounds = (live * nsx + slots - 1) / slots;
+    const int64_t rounds = (wgs * nsx + slots - 1) / slots;
     const double cost = (double)rounds * (kc / OKSTEP + 6) + (nsx > 1 ? 0.5 * nsx : 0.0);
     if (cost < bcost - 1e-9) {
       bcost = cost;
       best = nsx;
     }
   }
-  return best;
-}
-
-namespace {
-
-// Split of the paired upper-triangle kernel (one workgroup per slice and
-// split): the same makespan model.
-int ogemm_tn_pair_split(int K, int batch) {
-  const int64_t slots = ogemm_slots();
-  int best = 1;
-  double bcost = 1e300;
-  for (int ns = 1; ns <= 32; ++ns) {
-    int kc = (K + ns - 1) / ns;
-    kc = (kc + OKSTEP - 1) / OKSTEP * OKSTEP;
-    if (ns > 1 && kc < 16 * OKSTEP) break;
-    const int nsx = (K + kc - 1) / kc;
-    const int64_t rounds = ((int64_t)batch * nsx + slots - 1) / slots;
-    const double cost = (double)rounds * (kc / OKSTEP + 6) + (nsx > 1 ? 0.5 * nsx : 0.0);
-    if (cost < bcost - 1e-9) {
-      bcost = cost;
-      best = nsx;
-    }
-  }
+  if (cost_out) *cost_out = bcost;
   return best;
 }
 
 }  // namespace
 
 size_t ogemm_tn_part_bytes(int M, int K, int N, int batch) {
-  int ns = std::max(ogemm_tn_split(M, K, N, batch, false), ogemm_tn_split(M, K, N, batch, true));
-  if (M == N && N > 64 && N <= 120) ns = std::max(ns, ogemm_tn_pair_split(K, batch));
+  int ns = tn_split(tn_live_tiles(M, N, batch, false), K, 16);
+  if (M == N) ns = std::max(ns, tn_split(tn_live_tiles(M, N, batch, true), K, 16));
+  if (M == N && N > 64 && N <= 120) ns = std::max(ns, tn_split(batch, K, 32));
   return (size_t)ns * batch * M * N * 16;
 }
 
 hipError_t ogemm_tn(const float* X, int64_t lx, int64_t strideX, const float* Y, int64_t ly, int64_t strideY,
-                    double* part, int M, int N, int K, int batch, hipStream_t s, bool upper) {
+                    double* part, size_t part_bytes, int M, int N, int K, int batch, hipStream_t s, bool upper) {
   if (M <= 0 || N <= 0 || batch <= 0) return hipSuccess;
+  const size_t one = (size_t)batch * M * N * 16;
+  const int fit = (int)std::min<size_t>(32, part_bytes / one);
+  if (fit < 1) return hipErrorInvalidValue;
   OArgs a{};
   a.X = X;
   a.lx = 2 * lx;
@@ -628,35 +634,44 @@ hipError_t ogemm_tn(const float* X, int64_t lx, int64_t strideX, const float* Y,
   a.K = K;
   a.N = N;
   a.batch = batch;
-  a.nsplit = ogemm_tn_split(M, K, N, batch, upper && M == N);
+  a.xvec = 0;
+  a.upper = (upper && M <= N) ? 1 : 0;
+  // The upper-triangle kernel where the whole triangle is one block (64 < N
+  // <= 128); wider ones take it when the last chunk is full but for less than
+  // one row group (with 56 of 128 columns in it 3.8 ms against 2.9 for the
+  // three Grams of m = 440, 33 slices) and its longer workgroups (17 thin
+  // tiles per step and wave against 8 at 0.7 of the rate) still give the
+  // shorter makespan within the scratch at hand.
+  const int tblocks = tn_upper_blocks(M, N);
+  const int64_t live = tn_live_tiles(M, N, batch, a.upper != 0);
+  double ctri = 0, cgen = 0;
+  const int ntri = tn_split((int64_t)tblocks * batch, K, fit, &ctri);
+  const int ngen = tn_split(live, K, std::min(fit, 16), &cgen);
+  const bool tri = a.upper && N > 64 && (N <= 128 || ((127 & -N) < 16 && 17 * ctri < 8 / 0.7 * cgen));
+  a.nbig = tri ? tblocks : (M + 63) / 64;
+  a.mb = (M + 127) / 128;
+  a.nsplit = tri ? ntri : ngen;
   int kc = (K + a.nsplit - 1) / a.nsplit;
   kc = (kc + OKSTEP - 1) / OKSTEP * OKSTEP;
   a.kchunk = kc < OKSTEP ? OKSTEP : kc;
-  a.xvec = 0;
-  a.upper = (upper && M == N) ? 1 : 0;
-  const int TT = tn_thin_tiles(N, a.upper != 0);
   hipError_t e;
-  if (a.upper && N > 64 && N <= 120) {
-    a.nsplit = ogemm_tn_pair_split(K, batch);
-    kc = (K + a.nsplit - 1) / a.nsplit;
-    kc = (kc + OKSTEP - 1) / OKSTEP * OKSTEP;
-    a.kchunk = kc < OKSTEP ? OKSTEP : kc;
-    a.nsplit = (K + a.kchunk - 1) / a.kchunk;
-    a.nbig = 1;
-    a.nthin = 1;
-    a.total = a.nsplit * batch;
+  if (tri) {
+    const int64_t total = (int64_t)a.nbig * a.nsplit * batch;
+    if (total >= (int64_t)1 << 30) return hipErrorInvalidValue;
+    a.total = (int)total;
     a.per = (a.total + 7) / 8;
     const size_t lds = (size_t)2 * 16 * 16 * OSTRIDE * sizeof(double);
     static bool attr = false;
     if (!attr) {
-      (void)hipFuncSetAttribute((const void*)ogemm_tn_pair_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+      (void)hipFuncSetAttribute((const void*)ogemm_tn_upper_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)lds);
       (void)hipGetLastError();
       attr = true;
     }
-    hipLaunchKernelGGL(ogemm_tn_pair_kernel, dim3(8 * a.per), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(ogemm_tn_upper_kernel, dim3(8 * a.per), dim3(256), lds, s, a);
     e = hipGetLastError();
   } else {
+    const int TT = tn_thin_tiles(N, a.upper != 0);
     fill_grid(a, TT);
     e = olaunch<true>(a, TT, s);
   }

@@ -55,6 +55,7 @@ struct Plan {
   bool asplit;                  // BF16x3 with A_f transformed straight into (hi, lo) bf16 pairs
                                 // (KM_BF16X3_SPLIT; A_f is read only by the Krylov products)
   int ks_ax, ks_ahy;            // K splits of the Krylov products A X and A^H Y
+  size_t part_bytes;            // of o_part
   size_t kpart_bytes;           // their partials (K splits or tail splits)
   // workspace offsets (bytes)
   size_t o_canon, o_rout, o_xp;
@@ -135,6 +136,7 @@ int make_plan_tpinv(int64_t n1, int64_t n2, int64_t n3, int prec, Plan* p) {
   size_t part = (size_t)p->nsplit_g * F * rr * 16;
   if (p->dt == DT_F32 && n1 >= n2) part = ogemm_tn_part_bytes((int)r, (int)n1, (int)r, (int)F);
   p->o_part = take(part);
+  p->part_bytes = part;
   p->o_lam = take((size_t)F * r * 8);
   p->o_wd = take((size_t)F * rr * 16);
   p->o_wds = take((size_t)F * rr * 16);
@@ -277,6 +279,7 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
   }
   if (ritz) part = std::max(part, (size_t)p->nsplit_t * F * b * b * 16);
   p->o_part = take(part);
+  p->part_bytes = part;
   p->o_rinv = take((size_t)F * b * b * 16);
   p->o_chol = take(chol_uses_lds(b) ? 0 : (size_t)F * b * (b + 1) / 2 * 16);
   const bool need_svd = (op == TSVD_OP_RBK || op == TSVD_OP_APPROX || power || ritz);
@@ -432,8 +435,8 @@ int inner_products(const Ctx& c, const void* X, int64_t lx, int M, const void* Y
   const Plan& p = c.p;
   if (p.dt == DT_F32) {
     Timed tm_(cls, c.s);
-    HIPCHK(ogemm_tn(static_cast<const float*>(X), lx, strideX, static_cast<const float*>(Y), ly, strideY, part, M, N,
-                    (int)K, (int)p.F, c.s, upper));
+    HIPCHK(ogemm_tn(static_cast<const float*>(X), lx, strideX, static_cast<const float*>(Y), ly, strideY, part,
+                    p.part_bytes, M, N, (int)K, (int)p.F, c.s, upper));
     *nsum = 1;
     return TSVD_OK;
   }
@@ -1184,7 +1187,7 @@ int tqr_core(const Ctx& c, const void* A, int* nsum) {
     if ((r = orth_block(c, i))) return r;
   }
   return inner_products(c, c.at(p.o_q), p.m, (int)p.m, c.at(p.o_abar), p.n2, (int)p.n2, p.n1, p.n1 * p.m,
-                        p.n1 * p.n2, p.nsplit_r, p.kchunk_r, c.at<double>(p.o_part), nsum);
+                        p.n1 * p.n2, p.nsplit_r, p.kchunk_r, c.at<double>(p.o_part), nsum, K_GEMM_ORTH, true);
 }
 
 // Generic batched product C = alpha opA(A) opB(B) + beta C over the F slices
