@@ -110,6 +110,14 @@ inline bool chol_uses_lds(int64_t b) { return b * (b + 1) / 2 * 16 <= 120 * 1024
 // mode 1: the partials sum to an upper triangular R instead; the kernel only
 // inverts it (Rinv = R^{-1}).  mode 2 (b <= 128): only the upper triangle of
 // the partials is valid; G is its Hermitian extension.
+// Whole orthonormalisation of a small n x b block W per slice (in place if D is
+// W), one workgroup each: projection off the ib earlier columns Q, a shifted
+// CholeskyQR pass, the projection again, nshift shifted and nplain unshifted
+// passes.  orth_small_ok: the block fits (b <= 32, W and the coefficients in LDS).
+bool orth_small_ok(int64_t n, int64_t b, int64_t ib);
+hipError_t orth_small(DType dt, const void* W, int64_t ldw, int64_t strideW, const void* Q, int64_t ldq,
+                      int64_t strideQ, void* D, int64_t ldd, int64_t strideD, int n, int b, int ib, int nshift,
+                      int nplain, double shift, int batch, int* info, hipStream_t s);
 bool chol_blocked_ok(int b);  // the blocked factorisation (and mode 2) applies
 hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, void* gscratch, int b,
                        int batch, double shift_coef, int* info, hipStream_t s, int mode = 0);

@@ -505,6 +505,11 @@ int apply_rinv(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t ld
   return TSVD_OK;
 }
 
+// Shift of shifted CholeskyQR over the trace of the Gram matrix.
+double cholqr_shift(int64_t rows, int64_t b) {
+  return 11.0 * ((double)rows * b + (double)b * (b + 1)) * 0x1p-53;
+}
+
 // One CholeskyQR pass over a rows x b block (rows = n1 for the Krylov blocks,
 // n2 for Alg. 1's half-step iterates): dst = src R^{-1}, G = src^H src (+ shift).
 int cholqr_pass(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t ldd, bool shifted, int64_t rows) {
@@ -518,8 +523,7 @@ int cholqr_pass(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t l
                          long_rows ? p.nsplit_blk : p.nsplit_t, long_rows ? p.kchunk_blk : p.kchunk_t, part, &nsum,
                          K_GEMM_ORTH, upper);
   if (r) return r;
-  const double u = 1.1102230246251565e-16;
-  const double shift = shifted ? 11.0 * ((double)rows * p.b + (double)p.b * (p.b + 1)) * u : 0.0;
+  const double shift = shifted ? cholqr_shift(rows, p.b) : 0.0;
   {
     Timed tm_(K_CHOL, c.s);
     HIPCHK(chol_inv_ex(part, nsum, p.F * p.b * p.b, c.at<double>(p.o_rinv), c.at(p.o_chol), (int)p.b, (int)p.F,
@@ -645,6 +649,20 @@ int project_out_f32(const Ctx& c, void* W, int i) {
   return TSVD_OK;
 }
 
+// FP32 storage with FP64 Grams.  The shifted pass maps sigma_j(W) to
+// sigma_j / sqrt(sigma_j^2 + s), so kappa(X1) <= sqrt(alpha) kappa(W) with
+// alpha = s / ||W||^2 <= 11 (rows b + b (b + 1)) 2^-53 b, and an FP32 block
+// has kappa(W) below about 1e8 (its rounding noise).  One unshifted pass
+// then leaves an FP64 orthogonality error of about 2^-53 kappa(X1)^2; when
+// that bound stays within 16 FP32 roundings (2^-20), below the FP32 rounding
+// of the block itself in the 2-norm, a second unshifted pass cannot improve
+// the stored result and is left out (rows * b up to about 6e6 at b = 110).
+bool one_plain_pass(int64_t rows, int64_t b) {
+  const double u64 = 0x1p-53;
+  const double alpha_max = 11.0 * ((double)rows * b + (double)b * (b + 1)) * u64 * (double)b;
+  return alpha_max * u64 * 1e16 <= 0x1p-20;
+}
+
 // Shifted CholeskyQR3 of a rows x b block whose first pass has been done
 // (result in S1): dst = orthonormal basis of its range.
 int cholqr_finish(const Ctx& c, int64_t rows, void* dst, int64_t ldd) {
@@ -664,19 +682,20 @@ int cholqr_finish(const Ctx& c, int64_t rows, void* dst, int64_t ldd) {
     if ((r = cholqr_pass(c, S1, p.b, S0, p.b, false, rows))) return r;
     return cholqr_pass(c, S0, p.b, dst, ldd, false, rows);
   }
-  // FP32 storage with FP64 Grams.  The shifted pass maps sigma_j(W) to
-  // sigma_j / sqrt(sigma_j^2 + s), so kappa(X1) <= sqrt(alpha) kappa(W) with
-  // alpha = s / ||W||^2 <= 11 (rows b + b (b + 1)) 2^-53 b, and an FP32 block
-  // has kappa(W) below about 1e8 (its rounding noise).  One unshifted pass
-  // then leaves an FP64 orthogonality error of about 2^-53 kappa(X1)^2; when
-  // that bound stays within 16 FP32 roundings (2^-20), below the FP32 rounding
-  // of the block itself in the 2-norm, a second unshifted pass cannot improve
-  // the stored result and is left out (rows * b up to about 6e6 at b = 110).
-  const double u64 = 0x1p-53;
-  const double alpha_max = 11.0 * ((double)rows * p.b + (double)p.b * (p.b + 1)) * u64 * (double)p.b;
-  if (alpha_max * u64 * 1e16 <= 0x1p-20) return cholqr_pass(c, S1, p.b, dst, ldd, false, rows);
+  if (one_plain_pass(rows, p.b)) return cholqr_pass(c, S1, p.b, dst, ldd, false, rows);
   if ((r = cholqr_pass(c, S1, p.b, S0, p.b, false, rows))) return r;
   return cholqr_pass(c, S0, p.b, dst, ldd, false, rows);
+}
+
+// A block that one workgroup per slice orthonormalises whole.
+int orth_small_block(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t ldd, int64_t rows, int ib) {
+  const Plan& p = c.p;
+  const bool f64 = p.dt == DT_F64;
+  Timed tm_(K_GEMM_ORTH, c.s);
+  HIPCHK(orth_small(p.dt, src, lds, rows * lds, c.at(p.o_q), p.m, p.n1 * p.m, dst, ldd, rows * ldd, (int)rows,
+                    (int)p.b, ib, f64 ? 2 : 0, f64 ? 2 : one_plain_pass(rows, p.b) ? 1 : 2, cholqr_shift(rows, p.b),
+                    (int)p.F, c.info(), c.s));
+  return TSVD_OK;
 }
 
 // Orthonormalise the block in S0 against Q_<i and write it to Q(:, i b : (i+1) b).
@@ -688,6 +707,7 @@ int orth_block(const Ctx& c, int i, bool first32 = false) {
   void* S1 = c.at(p.o_s1);
   void* dst = c.at<unsigned char>(p.o_q) + (size_t)i * p.b * p.cs;
   int r;
+  if (orth_small_ok(p.n1, p.b, i * p.b)) return orth_small_block(c, S0, p.b, dst, p.m, p.n1, (int)(i * p.b));
   if ((r = (first32 && p.dt == DT_F32) ? project_out_f32(c, S0, i) : project_out(c, S0, i))) return r;
   if ((r = cholqr_pass(c, S0, p.b, S1, p.b, true, p.n1))) return r;
   if ((r = project_out(c, S1, i))) return r;
@@ -698,6 +718,7 @@ int orth_block(const Ctx& c, int i, bool first32 = false) {
 int orth_rows_n2(const Ctx& c, void* X) {
   const Plan& p = c.p;
   int r;
+  if (orth_small_ok(p.n2, p.b, 0)) return orth_small_block(c, X, p.b, X, p.b, p.n2, 0);
   if ((r = cholqr_pass(c, X, p.b, c.at(p.o_s1), p.b, true, p.n2))) return r;
   return cholqr_finish(c, p.n2, X, p.b);
 }
