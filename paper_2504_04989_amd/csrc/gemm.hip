@@ -70,6 +70,7 @@ __global__ __launch_bounds__(256) void zgemm_kernel(const GemmDesc d) {
   }
   const cx<TAs>* Ab = reinterpret_cast<const cx<TAs>*>(d.A) + (int64_t)f * d.strideA;
   const cx<TBs>* Bb = reinterpret_cast<const cx<TBs>*>(d.B) + (int64_t)f * d.strideB;
+  int64_t lda = d.lda, ldb = d.ldb;
 
   // Every read is issued without a branch at a clamped address, so that all
   // of a step's reads are in flight together: a clamped row or column feeds
@@ -85,13 +86,13 @@ __global__ __launch_bounds__(256) void zgemm_kernel(const GemmDesc d) {
 #pragma unroll
     for (int i = 0; i < EA; ++i) {
       const int gm = min(m0 + a_m(i), M - 1), gk = min(kt + a_k(i), kend - 1);
-      ld_cx<TAs, T>(Ab, AC ? ((int64_t)gk * d.lda + gm) : ((int64_t)gm * d.lda + gk), ra_r[i], ra_i[i]);
+      ld_cx<TAs, T>(Ab, AC ? ((int64_t)gk * lda + gm) : ((int64_t)gm * lda + gk), ra_r[i], ra_i[i]);
     }
     int64_t bidx[EB];
 #pragma unroll
     for (int i = 0; i < EB; ++i) {
       const int gn = min(n0 + b_n(i), N - 1), gk = min(kt + b_k(i), kend - 1);
-      bidx[i] = BC ? ((int64_t)gn * d.ldb + gk) : ((int64_t)gk * d.ldb + gn);
+      bidx[i] = BC ? ((int64_t)gn * ldb + gk) : ((int64_t)gk * ldb + gn);
       ld_cx<TBs, T>(Bb, bidx[i], rb_r[i], rb_i[i]);
     }
     if (BSUM) {
@@ -139,52 +140,63 @@ __global__ __launch_bounds__(256) void zgemm_kernel(const GemmDesc d) {
       acc_i[a][b] = acc_t{0, 0, 0, 0};
     }
 
-  if (kbeg < kend) {
-    gload(kbeg);
-    sstore(0, kbeg);
-  }
-  int buf = 0;
-  for (int kt = kbeg; kt < kend; kt += BK, buf ^= 1) {
-    __syncthreads();
-    const bool more = kt + BK < kend;
-    if (more) gload(kt + BK);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      const int kq = kk + q4;
-      T ar[TM], ai[TM], nai[TM], br[TN], bi[TN];
-#pragma unroll
-      for (int a = 0; a < TM; ++a) {
-        const int m = wm0 + a * 16 + r16;
-        const int s = AC ? (kq * SA + m) : (m * SA + kq);
-        ar[a] = sAr[buf][s];
-        ai[a] = sAi[buf][s];
-        nai[a] = -ai[a];
-      }
-#pragma unroll
-      for (int b = 0; b < TN; ++b) {
-        const int n = wn0 + b * 16 + r16;
-        const int s = BC ? (n * SB + kq) : (kq * SB + n);
-        br[b] = sBr[buf][s];
-        bi[b] = sBi[buf][s];
-      }
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc_r[a][b] = Mfma<T>::run(ar[a], br[b], acc_r[a][b]);
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc_i[a][b] = Mfma<T>::run(ar[a], bi[b], acc_i[a][b]);
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc_r[a][b] = Mfma<T>::run(nai[a], bi[b], acc_r[a][b]);
-#pragma unroll
-      for (int a = 0; a < TM; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b) acc_i[a][b] = Mfma<T>::run(ai[a], br[b], acc_i[a][b]);
+  for (int seg = 0;; ++seg) {
+    if (kbeg < kend) {
+      gload(kbeg);
+      sstore(0, kbeg);
     }
-    if (more) sstore(buf ^ 1, kt + BK);
+    int buf = 0;
+    for (int kt = kbeg; kt < kend; kt += BK, buf ^= 1) {
+      __syncthreads();
+      const bool more = kt + BK < kend;
+      if (more) gload(kt + BK);
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        const int kq = kk + q4;
+        T ar[TM], ai[TM], nai[TM], br[TN], bi[TN];
+#pragma unroll
+        for (int a = 0; a < TM; ++a) {
+          const int m = wm0 + a * 16 + r16;
+          const int s = AC ? (kq * SA + m) : (m * SA + kq);
+          ar[a] = sAr[buf][s];
+          ai[a] = sAi[buf][s];
+          nai[a] = -ai[a];
+        }
+#pragma unroll
+        for (int b = 0; b < TN; ++b) {
+          const int n = wn0 + b * 16 + r16;
+          const int s = BC ? (n * SB + kq) : (kq * SB + n);
+          br[b] = sBr[buf][s];
+          bi[b] = sBi[buf][s];
+        }
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) acc_r[a][b] = Mfma<T>::run(ar[a], br[b], acc_r[a][b]);
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) acc_i[a][b] = Mfma<T>::run(ar[a], bi[b], acc_i[a][b]);
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) acc_r[a][b] = Mfma<T>::run(nai[a], bi[b], acc_r[a][b]);
+#pragma unroll
+        for (int a = 0; a < TM; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b) acc_i[a][b] = Mfma<T>::run(ai[a], br[b], acc_i[a][b]);
+      }
+      if (more) sstore(buf ^ 1, kt + BK);
+    }
+    if (seg >= d.nmore) break;
+    const GemmDesc::More& e = d.more[seg];
+    Ab = reinterpret_cast<const cx<TAs>*>(e.A) + (int64_t)f * e.strideA;
+    Bb = reinterpret_cast<const cx<TBs>*>(e.B) + (int64_t)f * e.strideB;
+    lda = e.lda;
+    ldb = e.ldb;
+    kbeg = 0;
+    kend = e.K;
+    __syncthreads();  // every wave is done with the LDS of the product before
   }
 
   // epilogue
@@ -274,6 +286,7 @@ static hipError_t launch_conj(const GemmDesc& d, hipStream_t s) {
 hipError_t zgemm(const GemmDesc& d, hipStream_t s) {
   if (d.M <= 0 || d.N <= 0 || d.batch <= 0) return hipSuccess;
   if (d.nsplit > 1 && d.beta != 0.0) return hipErrorInvalidValue;
+  if (d.nmore < 0 || d.nmore > 2 || (d.nmore && (d.nsplit > 1 || d.b_nsum > 1))) return hipErrorInvalidValue;
   const DType a = d.ta, b = d.tb, c = d.tc, t = d.compute;
   if (a == DT_F32 && b == DT_F32 && c == DT_F32 && t == DT_F32) return launch_conj<float, float, float, float>(d, s);
   if (a == DT_F64 && b == DT_F64 && c == DT_F64 && t == DT_F64) return launch_conj<double, double, double, double>(d, s);

@@ -16,6 +16,8 @@ enum DType { DT_F32 = 0, DT_F64 = 1 };
 // b_nsum > 1: B is the sum of b_nsum matrices spaced b_sum_stride elements.
 // nsplit > 1: the K range is cut into nsplit chunks of kchunk; chunk s writes
 //   alpha * partial product to C + s * c_split_stride (beta must be 0).
+// nmore: further products of the same form and types, opA(A2) opB(B2) over K2,
+//   added to the first before C is written (no K split, no b_nsum).
 // Element counts (lda, strides, ...) are in complex elements.
 struct GemmDesc {
   const void* A; int64_t lda, strideA; DType ta; bool a_conj;
@@ -25,6 +27,8 @@ struct GemmDesc {
   int nsplit, kchunk; int64_t c_split_stride;
   double alpha, beta;
   DType compute;
+  struct More { const void* A; int64_t lda, strideA; const void* B; int64_t ldb, strideB; int K; } more[2];
+  int nmore;
 };
 hipError_t zgemm(const GemmDesc& d, hipStream_t s);
 
@@ -47,7 +51,7 @@ struct KGemmDesc {
   int N, batch, mode, nsplit;
   void* part;
   size_t part_bytes;  // size of part; a tail split is used only when it fits
-  int sub;            // C -= op(A) X instead of C = op(A) X (no K split, no tail split)
+  int acc;            // +1 / -1: C += / -= op(A) X instead of C = op(A) X
 };
 hipError_t kgemm(const KGemmDesc& d, hipStream_t s);
 // n complex FP32 values -> n (hi, lo) bf16 pairs (the KM_BF16X3_SPLIT form).
@@ -156,6 +160,8 @@ hipError_t sigma_from_lambda(const double* lambda, double* sigma, void* scx, int
 // FP64: P (batch x n2 x k, = T_f W_k) -> sigma_j = ||P(:, j)||, V = P / sigma
 // in place, sigma (FP64) and (sigma, 0) as complex double.
 hipError_t colnorm_sigma(void* P, int64_t n2, int k, int batch, double* sigma, void* scx, hipStream_t s);
+// out (rows x b, row stride ldo) += in (rows x b, dense), complex.
+hipError_t add_block(const void* in, void* out, int64_t rows, int b, int64_t ldo, DType t, hipStream_t s);
 // U * diag(sigma): Uout (batch x n1 x k) = Uin * sigma (per slice).
 hipError_t scale_cols_by(const void* Uin, const double* sigma, void* Uout, int64_t n1, int k, int batch, DType t,
                          hipStream_t s);

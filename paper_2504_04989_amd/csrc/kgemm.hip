@@ -59,7 +59,7 @@ struct KArgs {
   // rkchunk) and write their partials to part, one 128 x NCH block per
   // (tile, split).  rsplit == 0: no tail split.
   int nfull, nrem, rsplit, rkchunk;
-  int sub;  // C -= result (whole-K tiles written straight to C only)
+  float acc;  // +1 / -1: C += / -= result (0: C = result)
 };
 
 __device__ __forceinline__ uint32_t bf16_bits(float x) {
@@ -412,6 +412,7 @@ __global__ __launch_bounds__(256, 2) void kgemm_kernel(const KArgs a) {
   // ---- epilogue: accr / acci[i][u][r] = parts of C[col][n0 + 16 i + 4 q4 + r] ----
   float* out;
   int64_t ldo;
+  const bool into_c = rt < 0 && a.nsplit == 1;  // not a partial
   if (rt >= 0) {
     // tail split: the (tile, split) block of 128 big rows x NCH columns,
     // indexed from the tile's first row and column
@@ -437,9 +438,9 @@ __global__ __launch_bounds__(256, 2) void kgemm_kernel(const KArgs a) {
         for (int r = 0; r < 4; ++r) {
           if (n + r >= a.N) continue;
           float2* o = reinterpret_cast<float2*>(p + 2 * r);
-          if (a.sub) {
+          if (into_c && a.acc != 0.f) {
             const float2 c0 = *o;
-            *o = make_float2(c0.x - accr[i][u][r], c0.y - acci[i][u][r]);
+            *o = make_float2(fmaf(a.acc, accr[i][u][r], c0.x), fmaf(a.acc, acci[i][u][r], c0.y));
           } else {
             *o = make_float2(accr[i][u][r], acci[i][u][r]);
           }
@@ -468,9 +469,10 @@ __global__ void kgemm_split_thin_kernel(const float* __restrict__ X, int64_t ldx
   }
 }
 
-// C[f][row][n] = sum_s part[s][f][row][n] (fixed order), complex FP32.
+// C[f][row][n] = sum_s part[s][f][row][n] (fixed order), complex FP32, or added
+// to (acc = 1) or taken from (-1) what C holds.
 __global__ void kgemm_reduce_kernel(const float2* __restrict__ part, int nsplit, int batch, int M, int N,
-                                    float2* __restrict__ C, int64_t ldc, int64_t strideC) {
+                                    float2* __restrict__ C, int64_t ldc, int64_t strideC, float acc) {
   const int64_t per = (int64_t)M * N;
   const int64_t total = per * batch;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
@@ -482,7 +484,9 @@ __global__ void kgemm_reduce_kernel(const float2* __restrict__ part, int nsplit,
       s.x += v.x;
       s.y += v.y;
     }
-    C[f * strideC + (int64_t)row * ldc + n] = s;
+    float2* o = C + (f * strideC + (int64_t)row * ldc + n);
+    if (acc != 0.f) s = make_float2(fmaf(acc, s.x, o->x), fmaf(acc, s.y, o->y));
+    *o = s;
   }
 }
 
@@ -490,7 +494,7 @@ __global__ void kgemm_reduce_kernel(const float2* __restrict__ part, int nsplit,
 // (fixed order), written where the tile lies in C.
 __global__ void kgemm_tail_reduce_kernel(const float2* __restrict__ part, int nfull, int nrem, int rsplit, int nbig,
                                          int nthin, int brows, int nch, int M, int N, float2* __restrict__ C,
-                                         int64_t ldc, int64_t strideC) {
+                                         int64_t ldc, int64_t strideC, float acc) {
   const int64_t per = (int64_t)brows * nch;
   const int64_t total = per * nrem;
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
@@ -510,7 +514,9 @@ __global__ void kgemm_tail_reduce_kernel(const float2* __restrict__ part, int nf
       sum.x += v.x;
       sum.y += v.y;
     }
-    C[f * strideC + (int64_t)row * ldc + n] = sum;
+    float2* o = C + (f * strideC + (int64_t)row * ldc + n);
+    if (acc != 0.f) sum = make_float2(fmaf(acc, sum.x, o->x), fmaf(acc, sum.y, o->y));
+    *o = sum;
   }
 }
 
@@ -705,10 +711,9 @@ hipError_t kgemm(const KGemmDesc& d, hipStream_t s) {
   a.per = (a.total + 7) / 8;
   a.avec = ((d.lda & 1) == 0 && (d.strideA & 1) == 0 && ((uintptr_t)d.A & 15) == 0) ? 1 : 0;
   a.nfull = a.nrem = a.rsplit = a.rkchunk = 0;
-  a.sub = d.sub ? 1 : 0;
-  if (a.sub && a.nsplit > 1) return hipErrorInvalidValue;
+  a.acc = (float)d.acc;
   TailPlan tp{0, 0, 0, 0, 0};
-  if (a.nsplit == 1 && d.part && !a.sub) {
+  if (a.nsplit == 1 && d.part) {
     tp = kgemm_tail_plan(M, K, d.N, d.batch);
     if (tp.rsplit > 1 && d.part_bytes >= tp.bytes) {
       a.nfull = tp.nfull;
@@ -738,14 +743,15 @@ hipError_t kgemm(const KGemmDesc& d, hipStream_t s) {
     const int64_t n = (int64_t)a.nrem * (NWAVE * 16 * 2) * (8 * TT);
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(kgemm_tail_reduce_kernel, dim3(blocks), dim3(256), 0, s, (const float2*)d.part, a.nfull, a.nrem,
-                       a.rsplit, a.nbig, a.nthin, NWAVE * 16 * 2, 8 * TT, M, d.N, (float2*)d.C, d.ldc, d.strideC);
+                       a.rsplit, a.nbig, a.nthin, NWAVE * 16 * 2, 8 * TT, M, d.N, (float2*)d.C, d.ldc, d.strideC,
+                       a.acc);
     return hipGetLastError();
   }
   if (a.nsplit <= 1) return e;
   const int64_t n = (int64_t)M * d.N * d.batch;
   const int blocks = (int)std::min<int64_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(kgemm_reduce_kernel, dim3(blocks), dim3(256), 0, s, (const float2*)d.part, a.nsplit, d.batch, M,
-                     d.N, (float2*)d.C, d.ldc, d.strideC);
+                     d.N, (float2*)d.C, d.ldc, d.strideC, a.acc);
   return hipGetLastError();
 }
 

@@ -114,6 +114,29 @@ hipError_t scale_cols_by(const void* Uin, const double* sigma, void* Uout, int64
   return hipGetLastError();
 }
 
+// out (rows x b, row stride ldo) += in (rows x b, dense)
+template <typename T>
+__global__ void add_block_kernel(const cx<T>* in, cx<T>* out, int64_t total, int b, int64_t ldo) {
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= total) return;
+  const int64_t r = t / b;
+  cx<T>* o = out + r * ldo + (t - r * b);
+  const cx<T> x = in[t], y = *o;
+  *o = cx<T>{x.re + y.re, x.im + y.im};
+}
+hipError_t add_block(const void* in, void* out, int64_t rows, int b, int64_t ldo, DType t, hipStream_t s) {
+  const int64_t total = rows * b;
+  if (total == 0) return hipSuccess;
+  const dim3 g((unsigned)((total + 255) / 256));
+  if (t == DT_F64)
+    hipLaunchKernelGGL(add_block_kernel<double>, g, dim3(256), 0, s, (const cx<double>*)in, (cx<double>*)out, total, b,
+                       ldo);
+  else
+    hipLaunchKernelGGL(add_block_kernel<float>, g, dim3(256), 0, s, (const cx<float>*)in, (cx<float>*)out, total, b,
+                       ldo);
+  return hipGetLastError();
+}
+
 // sigma = sqrt(max(lambda, 0)) in FP64, and as complex (sigma, 0) in the
 // working precision for the inverse transform of the singular tubes.
 template <typename T>

@@ -292,7 +292,7 @@ __global__ __launch_bounds__(256, 2) void ogemm_kernel(const OArgs a) {
 // tile s of group w when 2 w <= s < tt, else the next tile of group 7 - w.
 // Bound by the FP64 matrix rate: 128 x 128 x 4096 over 33 slices 302 us with
 // 64-row tiles (MFMA busy 42%, half the product skipped for no gain) against
-// @G@ here; 256 x 256 x 4096: 1210 (64-column chunks) against @H@.
+// 185 here; 256 x 256 x 4096: 1210 (64-column chunks) against 1000.
 __global__ __launch_bounds__(256, 2) void ogemm_tn_upper_kernel(const OArgs a) {
   constexpr int SLOTS = 18;
   constexpr int TT = 16;

@@ -67,7 +67,7 @@ struct Plan {
   // m x m FP64 matrices, the modified cotangents U2 Pi + T H and T Pi
   size_t o_wall, o_lall, o_mm0, o_mm1, o_mm2, o_mm3, o_u2b, o_tp;
   size_t o_info, o_abar, o_obar, o_q, o_t, o_s0, o_s1, o_part, o_rinv, o_chol, o_lam, o_sig, o_wd, o_wds, o_heig,
-      o_uf, o_vf, o_scx, o_us, o_gbar, o_dbar, o_wraw, o_qbar, o_u2, o_zbar, o_wbar, o_tbar, o_kpart, o_kpack,
+      o_uf, o_vf, o_scx, o_us, o_gbar, o_dbar, o_wraw, o_qbar, o_u2, o_zbar, o_tbar, o_kpart, o_kpack,
       total;
 };
 
@@ -324,7 +324,6 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
   p->o_qbar = take(bwd ? (size_t)F * n1 * m * cs : 0);
   p->o_u2 = take(bwd ? (size_t)F * n2 * m * cs : 0);
   p->o_zbar = take(bwd ? (size_t)F * n1 * b * cs : 0);
-  p->o_wbar = take(bwd ? (size_t)F * n1 * b * cs : 0);
   p->o_tbar = take(bwd ? (size_t)F * n2 * b * cs : 0);
   {
     size_t kp = std::max(p->ks_ax > 1 ? (size_t)p->ks_ax * F * n1 * b * 8 : 0,
@@ -644,7 +643,7 @@ int project_out_f32(const Ctx& c, void* W, int i) {
   u.batch = (int)p.F;
   u.mode = KM_F32;
   u.nsplit = 1;
-  u.sub = 1;
+  u.acc = -1;
   HIPCHK(kgemm(u, c.s));
   return TSVD_OK;
 }
@@ -1250,13 +1249,57 @@ int gemm(const Ctx& c, int cls, Op A, Op B, void* C, int64_t ldc, int64_t stride
   return TSVD_OK;
 }
 
+// C (ldc) = or += op(B) X for a transformed n1 x n2 tensor B (A or the incoming
+// gradient) and a thin X of N columns, in the working precision.  FP32 takes
+// the Krylov-product kernel, which reads B once for all N columns, with the K
+// splits that part holds: 2000 x 2000 slices, 9 of them, N = 90 322 us in the
+// general kernel against 278, N = 30 159 against 110.
+int slice_gemm(const Ctx& c, const void* B, bool herm, const void* X, int64_t ldx, int64_t strideX, void* C,
+               int64_t ldc, int64_t strideC, int N, bool add, void* part, size_t part_bytes) {
+  const Plan& p = c.p;
+  const int M = (int)(herm ? p.n2 : p.n1), K = (int)(herm ? p.n1 : p.n2), F = (int)p.F;
+  if (p.dt != DT_F32)
+    return gemm(c, K_GEMM_KRYLOV, Op{B, p.n2, p.n1 * p.n2, p.dt, herm}, Op{X, ldx, strideX, p.dt, false}, C, ldc, strideC,
+                p.dt, M, N, K, 1.0, add ? 1.0 : 0.0, p.dt);
+  KGemmDesc k{};
+  k.A = B;
+  k.lda = p.n2;
+  k.strideA = p.n1 * p.n2;
+  k.rows = (int)p.n1;
+  k.cols = (int)p.n2;
+  k.herm = herm;
+  k.X = X;
+  k.ldx = ldx;
+  k.strideX = strideX;
+  k.C = C;
+  k.ldc = ldc;
+  k.strideC = strideC;
+  k.N = N;
+  k.batch = F;
+  k.mode = KM_F32;
+  k.acc = add ? 1 : 0;
+  k.nsplit = kgemm_split_balanced(M, K, N, F);
+  if (k.nsplit > 1 && kgemm_part_bytes(M, K, N, F, k.nsplit) > part_bytes) k.nsplit = 1;
+  k.part = part;
+  k.part_bytes = part_bytes;
+  Timed tm_(K_GEMM_KRYLOV, c.s);
+  HIPCHK(kgemm(k, c.s));
+  return TSVD_OK;
+}
+
 // Reverse pass of P(A) = Q Q^H A per Fourier slice (stabilised Krylov form):
 //   direct term Q Q^H G; Qbar = (G A^H + A G^H) Q; for i = q..0:
 //   Zbar_i = (I - Q_i Q_i^H) Qbar_i R_i^{-H} with R_i = Q_i^H W_i (the loss
 //   depends on Q_i only through its range); for i >= 1:
 //   Wbar_i = (I - Q_<i Q_<i^H) Zbar_i, Qbar_<i -= (Zbar_i W_i^H + W_i Zbar_i^H) Q_<i,
-//   Abar += Wbar_i T_i^H, Tbar_i = A^H Wbar_i, Abar += Q_{i-1} Tbar_i^H,
+//   Abar += Wbar_i T_{i-1}^H, Tbar_i = A^H Wbar_i, Abar += Q_{i-1} Tbar_i^H,
 //   Qbar_{i-1} += A Tbar_i; for i = 0: Abar += Zbar_0 Om^H.
+// The terms of Abar are collected and written by one pass at the end: Tbar_i is
+// added to column block i - 1 of U2 (or its truncated form), which Q multiplies,
+// and Wbar_i replaces Qbar_i, whose last reader is Zbar_i, so that
+//   Abar = Q U2'^H + Qbar_{1..q} T_{0..q-1}^H + Zbar_0 Om^H.
+// Term by term the n1 x n2 slices were written once and updated 2 q + 1 times
+// (2000 x 2000 x 16, b = 30, q = 2: 310 + 5 x 160 us; in one pass 500).
 int truncation_head(const Ctx& c, void* U2, void* Ub2, void* Tp);
 
 int proj_backward_impl(const Ctx& c, const void* A, const void* Omega, const void* G, void* dA,
@@ -1280,14 +1323,13 @@ int proj_backward_impl(const Ctx& c, const void* A, const void* Omega, const voi
   void* Db = c.at(p.o_dbar);
   void* U2 = c.at(p.o_u2);
   void* Zb = c.at(p.o_zbar);
-  void* Wb = c.at(p.o_wbar);
   void* Tb = c.at(p.o_tbar);
   double* part = c.at<double>(p.o_part);
   const size_t cs = p.cs;
   // U2 = Gbar^H Q (= Y^H, Y = Q^H Gbar); Dbar = Q U2^H (= Q Q^H Gbar)
-  if ((r = gemm(c, K_GEMM_KRYLOV, Op{Gb, n2, s12, dt, true}, Op{Q, m, s1m, dt, false}, U2, m, s2m, dt, n2, m, n1, 1.0,
-                0.0, dt)))
-    return r;
+  // (Dbar's memory holds the products' partials until the first term is written)
+  const size_t dbytes = (size_t)p.F * s12 * cs;
+  if ((r = slice_gemm(c, Gb, true, Q, m, s1m, U2, m, s2m, m, false, Db, dbytes))) return r;
   // the rank-k truncation replaces U2 by Cbar^H = U2 Pi + T H and T by T Pi
   // (truncation_head); the projection keeps them
   void* Ub2 = U2;
@@ -1297,16 +1339,9 @@ int proj_backward_impl(const Ctx& c, const void* A, const void* Omega, const voi
     Tq = c.at(p.o_tp);
     if ((r = truncation_head(c, U2, Ub2, Tq))) return r;
   }
-  if ((r = gemm(c, K_GEMM_LIFT, Op{Q, m, s1m, dt, false}, Op{Ub2, m, s2m, dt, true}, Db, n2, s12, dt, n1, n2, m, 1.0,
-                0.0, dt)))
-    return r;
   // Qbar = Gbar T + Abar U2   (T = Abar^H Q)
-  if ((r = gemm(c, K_GEMM_KRYLOV, Op{Gb, n2, s12, dt, false}, Op{Tq, m, s2m, dt, false}, Qb, m, s1m, dt, n1, m, n2,
-                1.0, 0.0, dt)))
-    return r;
-  if ((r = gemm(c, K_GEMM_KRYLOV, Op{Ab, n2, s12, dt, false}, Op{Ub2, m, s2m, dt, false}, Qb, m, s1m, dt, n1, m, n2,
-                1.0, 1.0, dt)))
-    return r;
+  if ((r = slice_gemm(c, Gb, false, Tq, m, s2m, Qb, m, s1m, m, false, Db, dbytes))) return r;
+  if ((r = slice_gemm(c, Ab, false, Ub2, m, s2m, Qb, m, s1m, m, true, Db, dbytes))) return r;
   const int ns = p.nsplit_blk, kc = p.kchunk_blk;
   int nsum = 1;
   for (int i = (int)p.q; i >= 0; --i) {
@@ -1329,18 +1364,13 @@ int proj_backward_impl(const Ctx& c, const void* A, const void* Omega, const voi
     if ((r = gemm(c, K_GEMM_ORTH, Op{Qbi, m, s1m, dt, false}, Op{c.at(p.o_rinv), b, (int64_t)b * b, DT_F64, true},
                   Zb, b, s1b, dt, n1, b, b, 1.0, 0.0, DT_F64)))
       return r;
-    if (i == 0) {
-      // Dbar += Zbar_0 Om^H
-      if ((r = gemm(c, K_GEMM_LIFT, Op{Zb, b, s1b, dt, false}, Op{c.at(p.o_obar), b, s2b, dt, true}, Db, n2, s12, dt,
-                    n1, n2, b, 1.0, 1.0, dt)))
-        return r;
-      break;
-    }
+    if (i == 0) break;
     const int ib = i * b;
-    // Wbar = Zbar - Q_<i (Q_<i^H Zbar)
-    HIPCHK(hipMemcpyAsync(Wb, Zb, (size_t)p.F * s1b * cs, hipMemcpyDeviceToDevice, c.s));
+    // Wbar = Zbar - Q_<i (Q_<i^H Zbar), in the place of Qbar_i
+    HIPCHK(hipMemcpy2DAsync(Qbi, (size_t)m * cs, Zb, (size_t)b * cs, (size_t)b * cs, (size_t)(p.F * p.n1),
+                            hipMemcpyDeviceToDevice, c.s));
     if ((r = inner_products(c, Q, m, ib, Zb, b, b, p.n1, s1m, s1b, ns, kc, part, &nsum))) return r;
-    if ((r = gemm(c, K_GEMM_ORTH, Op{Q, m, s1m, dt, false}, Op{part, b, (int64_t)ib * b, DT_F64, false}, Wb, b, s1b,
+    if ((r = gemm(c, K_GEMM_ORTH, Op{Q, m, s1m, dt, false}, Op{part, b, (int64_t)ib * b, DT_F64, false}, Qbi, m, s1m,
                   dt, n1, b, ib, -1.0, 1.0, DT_F64, nsum, p.F * ib * b)))
       return r;
     // Qbar_<i -= Zbar (W_i^H Q_<i) + W_i (Zbar^H Q_<i)
@@ -1352,25 +1382,41 @@ int proj_backward_impl(const Ctx& c, const void* A, const void* Omega, const voi
     if ((r = gemm(c, K_GEMM_ORTH, Op{Wi, m, s1m, dt, false}, Op{part, ib, (int64_t)b * ib, DT_F64, false}, Qb, m, s1m,
                   dt, n1, ib, b, -1.0, 1.0, DT_F64, nsum, p.F * b * ib)))
       return r;
-    unsigned char* Ti = T + (size_t)(i - 1) * b * cs;
-    unsigned char* Qi1 = Q + (size_t)(i - 1) * b * cs;
     unsigned char* Qbi1 = Qb + (size_t)(i - 1) * b * cs;
-    // Dbar += Wbar T_i^H
-    if ((r = gemm(c, K_GEMM_LIFT, Op{Wb, b, s1b, dt, false}, Op{Ti, m, s2m, dt, true}, Db, n2, s12, dt, n1, n2, b, 1.0,
-                  1.0, dt)))
-      return r;
-    // Tbar = Abar^H Wbar
-    if ((r = gemm(c, K_GEMM_KRYLOV, Op{Ab, n2, s12, dt, true}, Op{Wb, b, s1b, dt, false}, Tb, b, s2b, dt, n2, b, n1,
-                  1.0, 0.0, dt)))
-      return r;
-    // Dbar += Q_{i-1} Tbar^H
-    if ((r = gemm(c, K_GEMM_LIFT, Op{Qi1, m, s1m, dt, false}, Op{Tb, b, s2b, dt, true}, Db, n2, s12, dt, n1, n2, b, 1.0,
-                  1.0, dt)))
-      return r;
+    // Tbar = Abar^H Wbar, added to column block i - 1 of Ub2
+    if ((r = slice_gemm(c, Ab, true, Qbi, m, s1m, Tb, b, s2b, b, false, c.at(p.o_kpart), p.kpart_bytes))) return r;
+    {
+      Timed tm_(K_MISC, c.s);
+      HIPCHK(add_block(Tb, static_cast<unsigned char*>(Ub2) + (size_t)(i - 1) * b * cs, p.F * p.n2, b, m, dt, c.s));
+    }
     // Qbar_{i-1} += Abar Tbar
-    if ((r = gemm(c, K_GEMM_KRYLOV, Op{Ab, n2, s12, dt, false}, Op{Tb, b, s2b, dt, false}, Qbi1, m, s1m, dt, n1, b, n2,
-                  1.0, 1.0, dt)))
-      return r;
+    if ((r = slice_gemm(c, Ab, false, Tb, b, s2b, Qbi1, m, s1m, b, true, c.at(p.o_kpart), p.kpart_bytes))) return r;
+  }
+  {
+    GemmDesc d = gd();
+    d.A = Q;
+    d.lda = m;
+    d.strideA = s1m;
+    d.ta = dt;
+    d.B = Ub2;
+    d.ldb = m;
+    d.strideB = s2m;
+    d.tb = dt;
+    d.b_conj = true;
+    d.C = Db;
+    d.ldc = n2;
+    d.strideC = s12;
+    d.tc = dt;
+    d.M = n1;
+    d.N = n2;
+    d.K = m;
+    d.batch = (int)p.F;
+    d.compute = dt;
+    d.more[0] = {Zb, b, s1b, c.at(p.o_obar), b, s2b, b};
+    d.more[1] = {Qb + (size_t)b * cs, m, s1m, T, m, s2m, m - b};
+    d.nmore = p.q > 0 ? 2 : 1;
+    Timed tm_(K_GEMM_LIFT, c.s);
+    HIPCHK(zgemm(d, c.s));
   }
   {
     Timed tm_(K_FFT_INV, c.s);
@@ -2090,7 +2136,7 @@ int tsvd_diag_kgemm_sub(const void* A, const void* X, void* C, int64_t rows, int
   d.batch = (int)batch;
   d.mode = KM_F32;
   d.nsplit = 1;
-  d.sub = 1;
+  d.acc = -1;
   HIPCHK(kgemm(d, (hipStream_t)stream));
   return TSVD_OK;
 }
