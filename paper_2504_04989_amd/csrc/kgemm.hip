@@ -633,40 +633,53 @@ size_t kgemm_part_bytes(int M, int K, int N, int batch, int nsplit) {
   return kgemm_tail_plan(M, K, N, batch).bytes;
 }
 
-int kgemm_split(int M, int K, int N, int batch, int* kchunk) {
-  const int TT = kgemm_thin_tiles(N);
-  const int64_t nthin = (N + 8 * TT - 1) / (8 * TT);
-  const int64_t nbig = (M + NWAVE * 16 * 2 - 1) / (NWAVE * 16 * 2);
-  const int64_t tiles = nthin * nbig * batch;
-  int ns = 1;
-  while (tiles * ns < 512 && ns < 8 && (int64_t)K / (2 * ns) >= 256) ns *= 2;
+namespace {
+
+// Makespan of a product of `tiles` tiles in ns splits, in K steps: rounds over
+// the workgroup slots x (steps per split + a workgroup's fixed cost, 6 steps).
+double split_cost(int64_t tiles, int K, int ns) {
   int kc = (K + ns - 1) / ns;
   kc = (kc + KSTEP - 1) / KSTEP * KSTEP;
-  ns = (K + kc - 1) / kc;
-  if (ns < 1) ns = 1;
-  *kchunk = kc < KSTEP ? KSTEP : kc;
-  return ns;
+  if ((K + kc - 1) / kc != ns) return 1e300;  // the chunking gives fewer splits
+  const int64_t rounds = (tiles * ns + kgemm_slots() - 1) / kgemm_slots();
+  return (double)rounds * (kc / KSTEP + 6);
+}
+
+int64_t kgemm_tiles(int M, int N, int batch) {
+  const int TT = kgemm_thin_tiles(N);
+  return (int64_t)((N + 8 * TT - 1) / (8 * TT)) * ((M + NWAVE * 16 * 2 - 1) / (NWAVE * 16 * 2)) * batch;
+}
+
+}  // namespace
+
+int kgemm_split(int M, int K, int N, int batch, bool narrow) {
+  const int64_t tiles = kgemm_tiles(M, N, batch);
+  int least = 1;
+  while (tiles * least < 512 && least < 8 && (int64_t)K / (2 * least) >= 256) least *= 2;
+  const int kc = ((K + least - 1) / least + KSTEP - 1) / KSTEP * KSTEP;
+  least = std::max((K + kc - 1) / kc, 1);
+  if (narrow || tiles >= kgemm_slots()) return least;
+  // fewer splits than that are not taken even where they are as fast: the
+  // partial sums they add up are longer, and so is their rounding error
+  int best = least;
+  double best_cost = split_cost(tiles, K, least) + (least > 1 ? 8 + 0.25 * least : 0);
+  for (int ns = least + 1; ns <= 16; ++ns) {
+    // 8 steps and the partials' traffic for the reduction's launch
+    const double cost = split_cost(tiles, K, ns) + 8 + 0.25 * ns;
+    if (cost < best_cost) {
+      best_cost = cost;
+      best = ns;
+    }
+  }
+  return best;
 }
 
 int kgemm_split_balanced(int M, int K, int N, int batch) {
-  static int slots = 0;
-  if (!slots) {
-    int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) !=
-                                                 hipSuccess || cus <= 0)
-      cus = 256;
-    slots = 2 * cus;  // two workgroups per CU (launch bounds)
-  }
-  const int TT = kgemm_thin_tiles(N);
-  const int64_t tiles = (int64_t)((N + 8 * TT - 1) / (8 * TT)) * ((M + NWAVE * 16 * 2 - 1) / (NWAVE * 16 * 2)) * batch;
+  const int64_t tiles = kgemm_tiles(M, N, batch);
   int best = 1;
   double best_cost = 1e300;
   for (int ns = 1; ns <= 16; ++ns) {
-    int kc = (K + ns - 1) / ns;
-    kc = (kc + KSTEP - 1) / KSTEP * KSTEP;
-    if ((K + kc - 1) / kc != ns) continue;  // the chunking gives fewer splits
-    const int64_t rounds = (tiles * ns + slots - 1) / slots;
-    const double cost = (double)rounds * (kc / KSTEP + 6);
+    const double cost = split_cost(tiles, K, ns);
     if (cost < best_cost) {
       best_cost = cost;
       best = ns;

@@ -225,10 +225,16 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
   p->asplit = p->kmode == KM_BF16X3 && p->dt == DT_F32 && fft_reg_supported((int)n3, DT_F32) &&
               (op == TSVD_OP_RBK || op == TSVD_OP_APPROX || op == TSVD_OP_POWER || op == TSVD_OP_POWER_APPROX ||
                ritz);
-  int kc_unused;
   if (p->kmode != KM_BF16) {
-    p->ks_ax = p->dt == DT_F32 ? kgemm_split((int)n1, (int)n2, (int)b, (int)F, &kc_unused) : 1;
-    p->ks_ahy = p->dt == DT_F32 ? kgemm_split((int)n2, (int)n1, (int)b, (int)F, &kc_unused) : 1;
+    // Sizes that the entry without a workspace may take (64 MiB in all) keep
+    // the scratch of the narrow splits; the others take as many as pay: a Krylov
+    // product of 512 x 768 x 3, b = 60 (2 slices) 53 us in 2 splits, 25 in 16; 1000
+    // x 1000 x 32, b = 60 151 us in 2, 113 in 3.
+    // BF16x3 keeps them too: its products' sums stay in their order.
+    const bool narrow = p->kmode != KM_F32 ||
+                        (op == TSVD_OP_RBK && (size_t)F * n1 * n2 * 8 <= (size_t)TSVD_NOALLOC_SCRATCH_BYTES);
+    p->ks_ax = p->dt == DT_F32 ? kgemm_split((int)n1, (int)n2, (int)b, (int)F, narrow) : 1;
+    p->ks_ahy = p->dt == DT_F32 ? kgemm_split((int)n2, (int)n1, (int)b, (int)F, narrow) : 1;
   } else {
     p->ks_ax = kgemm_bf16_split((int)n1, (int)n2, (int)b, (int)F);
     p->ks_ahy = kgemm_bf16_split((int)n2, (int)n1, (int)b, (int)F);
@@ -1278,7 +1284,7 @@ int slice_gemm(const Ctx& c, const void* B, bool herm, const void* X, int64_t ld
   k.batch = F;
   k.mode = KM_F32;
   k.acc = add ? 1 : 0;
-  k.nsplit = kgemm_split_balanced(M, K, N, F);
+  k.nsplit = kgemm_split(M, K, N, F, false);
   if (k.nsplit > 1 && kgemm_part_bytes(M, K, N, F, k.nsplit) > part_bytes) k.nsplit = 1;
   k.part = part;
   k.part_bytes = part_bytes;
