@@ -70,6 +70,16 @@ __device__ __forceinline__ T wave_sum(T v) {
   return (lane_value(v, 0) + lane_value(v, 16)) + (lane_value(v, 32) + lane_value(v, 48));
 }
 
+// Sum over the 32 lanes of each half (all 64 active), in every lane of the half.
+__device__ __forceinline__ double half_sum(double v) {
+  v += dpp_mov<0xB1>(v);
+  v += dpp_mov<0x4E>(v);
+  v += dpp_mov<0x141>(v);
+  v += dpp_mov<0x140>(v);
+  const double lo = lane_value(v, 0) + lane_value(v, 16), hi = lane_value(v, 32) + lane_value(v, 48);
+  return (threadIdx.x & 32) ? hi : lo;
+}
+
 // Workgroup barrier for data exchanged through LDS alone: unlike
 // __syncthreads() it does not wait for the wave's global stores to complete
 // (about a microsecond in a step that has just stored a result).

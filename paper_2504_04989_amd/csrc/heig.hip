@@ -1343,24 +1343,33 @@ __global__ __launch_bounds__(256) void heig_backxf_kernel(int m, int k, unsigned
 // fetched into registers while the current one is applied), one workgroup
 // barrier per group: the NB reflectors of a group are applied in order
 // with no barrier between them, since no half-wave reads another's column.
+// Bound by the chain of one reflector: S LDS reads, S dependent FMAs, the lane
+// sum, S more.  Reflectors are stored over all 32 S rows with their zeros, so
+// that no read is conditional, the scalar factors lie in LDS, and the sum goes
+// through DPP: 78 us for 180 rows (2 slices), 14 for 30 (9 slices), 147 for 150
+// (129 slices), where guarded reads, factors from memory and LDS shuffles took
+// 191, 31 and 356.
 template <int S, int NB>
 __global__ __launch_bounds__(256) void heig_backxf2_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
                                                            cx<double>* __restrict__ Wout) {
+  constexpr int MP = 32 * S;
   extern __shared__ __align__(16) unsigned char smem[];
-  cx<double>* vbuf = reinterpret_cast<cx<double>*>(smem);  // 2 groups x NB x m
+  cx<double>* vbuf = reinterpret_cast<cx<double>*>(smem);  // 2 groups x NB x MP
+  cx<double>* tau = vbuf + 2 * NB * MP;                    // MP
   const int f = blockIdx.x;
   const int tid = threadIdx.x, g = tid >> 5, l32 = tid & 31;
   const int col = blockIdx.y * 8 + g;
   const bool colok = col < k;
   HeigView hv = heig_view(scratch, per_slice, f, m);
   cx<double>* W = Wout + (int64_t)f * m * k;
+  for (int i = tid; i < m - 1; i += 256) tau[i] = hv.tau[i];
   cx<double> w[S];
 #pragma unroll
   for (int s = 0; s < S; ++s) {
     const int r = l32 + 32 * s;
     w[s] = (colok && r < m) ? W[(int64_t)r * k + col] : cx<double>{0, 0};
   }
-  constexpr int PF = 4;  // reflector entries per thread and reflector (m <= 1024)
+  constexpr int PF = (MP + 255) / 256;  // rows per thread and reflector
   // reflectors j0 .. 0 in descending order; group q holds j = j0 - q NB - u, u < NB
   const int j0 = m - 2;
   const int ng = (j0 + NB) / NB;
@@ -1368,56 +1377,44 @@ __global__ __launch_bounds__(256) void heig_backxf2_kernel(int m, int k, unsigne
   auto fetch = [&](int q) {
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
-      const int j = j0 - q * NB - u;
-      const int L = m - j - 1;
-      const cx<double>* vg = hv.A + (int64_t)(j >= 0 ? j : 0) * m + (j + 1);
+      const int j = max(j0 - q * NB - u, 0);
 #pragma unroll
-      for (int p = 0; p < PF; ++p) {
-        const int i = tid + p * 256;
-        pre[u][p] = (j >= 0 && i < L) ? vg[i] : cx<double>{0, 0};
-      }
+      for (int p = 0; p < PF; ++p) pre[u][p] = hv.A[(int64_t)j * m + min(max(tid + p * 256, j + 1), m - 1)];
     }
   };
   auto stage = [&](int q) {
-    cx<double>* vb = vbuf + (size_t)(q & 1) * NB * m;
+    cx<double>* vb = vbuf + (q & 1) * NB * MP;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int j = j0 - q * NB - u;
-      const int L = m - j - 1;
 #pragma unroll
       for (int p = 0; p < PF; ++p) {
-        const int i = tid + p * 256;
-        if (j >= 0 && i < L) vb[(size_t)u * m + i] = pre[u][p];
+        const int r = tid + p * 256;
+        if (r < MP) vb[u * MP + r] = r > j && r < m ? pre[u][p] : cx<double>{0, 0};
       }
     }
   };
   auto apply = [&](int j, const cx<double>* vb) {
-    const cx<double> tau = hv.tau[j];
-    if (tau.re == 0.0 && tau.im == 0.0) return;
-    // rows r = j + 1 + i of the reflector; row r of W sits in w[(r - l32) / 32].
-    // The lane's entries of the reflector are read from LDS once, for both
-    // the product and the update.
+    const cx<double> t = tau[j];
+    if (t.re == 0.0 && t.im == 0.0) return;
+    // the lane's entries of the reflector are read from LDS once, for both
+    // the product and the update
     cx<double> vv[S];
-    double sr = 0, si = 0;
+#pragma unroll
+    for (int s = 0; s < S; ++s) vv[s] = vb[l32 + 32 * s];
+    double a0 = 0, a1 = 0, b0 = 0, b1 = 0;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const int i = l32 + 32 * s - j - 1;
-      vv[s] = (i >= 0 && i < m - j - 1) ? vb[i] : cx<double>{0, 0};
-      const cx<double> t = cjmul(vv[s], w[s]);
-      sr += t.re;
-      si += t.im;
+      a0 = fma(vv[s].re, w[s].re, a0);
+      b0 = fma(vv[s].re, w[s].im, b0);
+      a1 = fma(vv[s].im, w[s].im, a1);
+      b1 = fma(vv[s].im, w[s].re, b1);
     }
-#pragma unroll
-    for (int o = 16; o > 0; o >>= 1) {
-      sr += __shfl_xor(sr, o, 64);
-      si += __shfl_xor(si, o, 64);
-    }
-    const cx<double> sc = cmulc(tau, cx<double>{sr, si});
+    const cx<double> sc = cmulc(t, cx<double>{half_sum(a0 + a1), half_sum(b0 - b1)});
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-      const cx<double> t = cmulc(vv[s], sc);
-      w[s].re -= t.re;
-      w[s].im -= t.im;
+      w[s].re = fma(-vv[s].re, sc.re, fma(vv[s].im, sc.im, w[s].re));
+      w[s].im = fma(-vv[s].re, sc.im, fma(-vv[s].im, sc.re, w[s].im));
     }
   };
   if (ng > 0) {
@@ -1427,17 +1424,17 @@ __global__ __launch_bounds__(256) void heig_backxf2_kernel(int m, int k, unsigne
   }
   __syncthreads();
   for (int q = 0; q < ng; ++q) {
-    const cx<double>* vb = vbuf + (size_t)(q & 1) * NB * m;
+    const cx<double>* vb = vbuf + (q & 1) * NB * MP;
 #pragma unroll
     for (int u = 0; u < NB; ++u) {
       const int j = j0 - q * NB - u;
-      if (j >= 0) apply(j, vb + (size_t)u * m);
+      if (j >= 0) apply(j, vb + u * MP);
     }
     if (q + 1 < ng) {
       stage(q + 1);
       if (q + 2 < ng) fetch(q + 2);
     }
-    __syncthreads();
+    lds_barrier();
   }
 #pragma unroll
   for (int s = 0; s < S; ++s) {
@@ -1597,15 +1594,27 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
   // 4. back-transformation
   const size_t sm4 = ((size_t)m * 8 + m) * sizeof(cx<double>);
   if (stages & HEIG_BACKXF) {
-    // two LDS groups of NB reflectors: 4 up to m = 448 (56 KB), 2 above
-    const size_t sm5a = (size_t)2 * 4 * m * sizeof(cx<double>), sm5b = (size_t)2 * 2 * m * sizeof(cx<double>);
+    // two LDS groups of NB reflectors over the padded rows: 4 up to m = 448 (63
+    // KB with the factors), 2 above
     const dim3 g5(batch, (k + 7) / 8);
-    if (m <= 8 * 32)
-      hipLaunchKernelGGL((heig_backxf2_kernel<8, 4>), g5, dim3(256), sm5a, s, m, k, sc, per, (cx<double>*)W);
-    else if (m <= 14 * 32)
-      hipLaunchKernelGGL((heig_backxf2_kernel<14, 4>), g5, dim3(256), sm5a, s, m, k, sc, per, (cx<double>*)W);
-    else if (m <= 20 * 32)
-      hipLaunchKernelGGL((heig_backxf2_kernel<20, 2>), g5, dim3(256), sm5b, s, m, k, sc, per, (cx<double>*)W);
+#define TSVD_BACKXF(S, NB)                                                                                     \
+  hipLaunchKernelGGL((heig_backxf2_kernel<S, NB>), g5, dim3(256), (2 * NB + 1) * 32 * S * sizeof(cx<double>), s, m, k, \
+                     sc, per, (cx<double>*)W)
+    if (m <= 32)
+      TSVD_BACKXF(1, 4);
+    else if (m <= 64)
+      TSVD_BACKXF(2, 4);
+    else if (m <= 128)
+      TSVD_BACKXF(4, 4);
+    else if (m <= 192)
+      TSVD_BACKXF(6, 4);
+    else if (m <= 256)
+      TSVD_BACKXF(8, 4);
+    else if (m <= 448)
+      TSVD_BACKXF(14, 4);
+    else if (m <= 640)
+      TSVD_BACKXF(20, 2);
+#undef TSVD_BACKXF
     else
       hipLaunchKernelGGL(heig_backxf_kernel, dim3(batch, (k + 7) / 8), dim3(256), sm4, s, m, k, sc, per,
                          (cx<double>*)W);
