@@ -164,33 +164,54 @@ hipError_t sigma_from_lambda(const double* lambda, double* sigma, void* scx, int
 // as FP64 and as complex (sigma, 0).  ||T_f w_j|| = ||C_f^H w_j|| is sigma_j
 // to a relative accuracy of about u sigma_1 / sigma_j, where sqrt(lambda_j)
 // carries the Gram's absolute error m u lambda_1 / (2 lambda_j).
-__global__ void colnorm_sigma_kernel(cx<double>* __restrict__ P, int64_t n2, int k, int64_t total,
-                                     double* __restrict__ sigma, cx<double>* __restrict__ scx) {
-  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= total) return;
-  const int c = (int)(t % k);
-  const int64_t f = t / k;
-  cx<double>* col = P + f * n2 * k + c;
+// Bound by the latency of the column's reads: 16 threads share a column (rows
+// r16 + 16 i), 16 columns to a workgroup, eight reads of a thread in flight.
+// With the phase kernels below it took 84 us of a 64 x 64 x 16 call and 242 of a
+// 256^3 one (45 columns) with one thread per column and its reads in turn; now
+// 55 and 123.
+__global__ __launch_bounds__(256) void colnorm_sigma_kernel(cx<double>* __restrict__ P, int64_t n2, int k,
+                                                            int64_t total, double* __restrict__ sigma,
+                                                            cx<double>* __restrict__ scx) {
+  __shared__ double part[16][17];
+  const int cl = threadIdx.x % 16, rl = threadIdx.x / 16;
+  const int64_t t = (int64_t)blockIdx.x * 16 + cl, tc = min(t, total - 1);
+  cx<double>* col = P + (tc / k) * n2 * k + tc % k;
   double ss = 0.0;
-  for (int64_t i = 0; i < n2; ++i) {
-    const cx<double> v = col[i * k];
-    ss += v.re * v.re + v.im * v.im;
+  for (int64_t i0 = rl; i0 < n2; i0 += 8 * 16) {
+    cx<double> v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = col[min(i0 + 16 * u, n2 - 1) * k];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (i0 + 16 * u < n2) ss += v[u].re * v[u].re + v[u].im * v[u].im;
   }
+  part[rl][cl] = ss;
+  __syncthreads();
+  ss = 0.0;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) ss += part[r][cl];
+  if (t >= total) return;
   const double sg = sqrt(ss);
   if (sg > 0) {
     const double inv = 1.0 / sg;
-    for (int64_t i = 0; i < n2; ++i) {
-      cx<double> v = col[i * k];
-      col[i * k] = cx<double>{v.re * inv, v.im * inv};
+    for (int64_t i0 = rl; i0 < n2; i0 += 8 * 16) {
+      cx<double> v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = col[min(i0 + 16 * u, n2 - 1) * k];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (i0 + 16 * u < n2) col[(i0 + 16 * u) * k] = cx<double>{v[u].re * inv, v[u].im * inv};
     }
   }
-  sigma[t] = sg;
-  scx[t] = cx<double>{sg, 0.0};
+  if (rl == 0) {
+    sigma[t] = sg;
+    scx[t] = cx<double>{sg, 0.0};
+  }
 }
 hipError_t colnorm_sigma(void* P, int64_t n2, int k, int batch, double* sigma, void* scx, hipStream_t s) {
   const int64_t total = (int64_t)batch * k;
   if (total == 0) return hipSuccess;
-  hipLaunchKernelGGL(colnorm_sigma_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (cx<double>*)P,
+  hipLaunchKernelGGL(colnorm_sigma_kernel, dim3((unsigned)((total + 15) / 16)), dim3(256), 0, s, (cx<double>*)P,
                      n2, k, total, sigma, (cx<double>*)scx);
   return hipGetLastError();
 }
@@ -380,12 +401,19 @@ __global__ __launch_bounds__(256) void canon_colmax_kernel(const cx<T>* __restri
   for (int j = threadIdx.x; j < k; j += blockDim.x) {
     T best = -1;
     int bi = 0x7fffffff;
-    for (int64_t i = r0; i < r1; ++i) {
-      const cx<T> a = u[i * k + j];
-      const T m2 = a.re * a.re + a.im * a.im;
-      if (m2 > best) {
-        best = m2;
-        bi = (int)i;
+    // eight reads in flight (rows past the end repeat the last one, which is
+    // not above itself)
+    for (int64_t i0 = r0; i0 < r1; i0 += 8) {
+      cx<T> a[8];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) a[t] = u[min(i0 + t, r1 - 1) * k + j];
+#pragma unroll
+      for (int t = 0; t < 8; ++t) {
+        const T m2 = a[t].re * a[t].re + a[t].im * a[t].im;
+        if (m2 > best) {
+          best = m2;
+          bi = (int)(i0 + t);
+        }
       }
     }
     pv[(f * nch + ch) * k + j] = (double)best;
