@@ -10,21 +10,38 @@
 // rounded once on store).  One workgroup owns 2*NP consecutive tubes.  The tubes are read from HBM
 // with fully coalesced loads, two real tubes are packed into one complex
 // sequence z = x_a + i x_b in LDS, a self-sorting (Stockham) mixed-radix FFT
-// with radices 2, 3, 4, 5, 7, 11, 13 runs out of LDS, and the two real
+// with radices 2, 3, 4, 5, 7, 11, 13 and, for larger prime factors, a
+// general pass runs out of LDS, and the two real
 // spectra are separated with X_a[f] = (Z[f] + conj Z[-f]) / 2,
 // X_b[f] = (Z[f] - conj Z[-f]) / (2i) while writing the slice-major output
 // (coalesced across tubes).  The inverse packs two Hermitian half spectra
-// the same way.  Lengths with a prime factor above 13 use a direct DFT.
+// the same way.  Lengths whose sequences do not fit LDS use a direct DFT.
+//
+// What bounds the general kernels is instruction issue and the latency of the
+// tube reads (two workgroups per CU): reads are issued eight at a time,
+// divisions by runtime lengths are multiplications, odd radices pair their
+// terms.  512 x 512 tubes of 200 FP32 samples: 427 us forward, 279 inverse,
+// against 553 and 431 with one read at a time, hardware division and full
+// products; 160 000 tubes of 191 (prime; before, one sincos per term): 1901 and
+// 1941 us against 48244 and 7727.
 #include "common.h"
 #include "kernels.h"
 
 namespace tsvd {
 
+// Quotient by a runtime divisor d >= 1 as a multiplication: exact while n d < 2^32.
+struct Div {
+  uint64_t mul;
+  uint32_t d;
+  __device__ __forceinline__ int quot(int n) const { return (int)(((uint64_t)(uint32_t)n * mul) >> 32); }
+};
+static Div make_div(int d) { return Div{(((uint64_t)1 << 32) / (uint32_t)d) + 1, (uint32_t)d}; }
+
 struct FftPlan {
   int N;
   int nf;
   int fac[24];
-  int direct;  // 1: no supported factorisation, use the direct DFT
+  Div dN, dNs[24], dnb[24];  // by N, and for each pass by Ns and N / R
 };
 
 static FftPlan make_plan(int N) {
@@ -37,7 +54,20 @@ static FftPlan make_plan(int N) {
       p.fac[p.nf++] = r;
       n /= r;
     }
-  p.direct = (n != 1);
+  for (int r = 17; n > 1; r += 2) {  // the prime factors above 13: general passes
+    if (r * r > n) r = n;
+    while (n % r == 0 && p.nf < 24) {
+      p.fac[p.nf++] = r;
+      n /= r;
+    }
+  }
+  p.dN = make_div(N);
+  int Ns = 1;
+  for (int s = 0; s < p.nf; ++s) {
+    p.dNs[s] = make_div(Ns);
+    p.dnb[s] = make_div(N / p.fac[s]);
+    Ns *= p.fac[s];
+  }
   return p;
 }
 
@@ -62,17 +92,24 @@ __device__ void make_twiddles(cx<T>* tw, int N) {
 
 // One Stockham pass with radix R: Ns = product of the radices already done.
 // Butterfly j of a length-N sequence reads in[j + r N/R], multiplies by the
-// twiddle w^(r k N/(Ns R)) (k = j mod Ns), takes a length-R DFT and writes
-// out[(j / Ns) Ns R + k + r Ns].
+// twiddle w^(r k N/(Ns R)) (k = j mod Ns; the exponent stays below N), takes a
+// length-R DFT and writes out[(j / Ns) Ns R + k + r Ns].
 template <typename T, bool INV, int R>
-__device__ void stockham_pass(const cx<T>* in, cx<T>* out, const cx<T>* tw, int N, int Ns, int NP) {
+__device__ void stockham_pass(const cx<T>* in, cx<T>* out, const cx<T>* tw, int N, int Ns, Div dNs, Div dnb, int NP) {
   const int nb = N / R;
-  const int tws = N / (Ns * R);
-  const int SP = N + 1;  // padded sequence stride (LDS banks)
+  const int tws = (int)dNs.quot(nb);  // N / (Ns R)
+  const int SP = N + 1;               // padded sequence stride (LDS banks)
+  constexpr int H = (R - 1) / 2;
+  cx<T> wr[R];  // exp(-+2 pi i r / R)
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    wr[r] = R == 2 || R == 4 ? cx<T>{1, 0} : tw[r * nb];
+    if (INV) wr[r].im = -wr[r].im;
+  }
   for (int idx = threadIdx.x; idx < NP * nb; idx += blockDim.x) {
-    const int p = idx / nb;
+    const int p = dnb.quot(idx);
     const int j = idx - p * nb;
-    const int k = j % Ns;
+    const int jq = dNs.quot(j), k = j - jq * Ns;
     const cx<T>* a = in + p * SP;
     cx<T>* o = out + p * SP;
     cx<T> v[R];
@@ -80,17 +117,17 @@ __device__ void stockham_pass(const cx<T>* in, cx<T>* out, const cx<T>* tw, int 
     for (int r = 0; r < R; ++r) {
       cx<T> x = a[j + r * nb];
       if (r > 0) {
-        cx<T> w = tw[(r * k * tws) % N];
+        cx<T> w = tw[r * k * tws];
         if (INV) w = cconj(w);
         x = cmul(x, w);
       }
       v[r] = x;
     }
     cx<T> V[R];
-    if (R == 2) {
+    if constexpr (R == 2) {
       V[0] = cx<T>{v[0].re + v[1].re, v[0].im + v[1].im};
       V[1] = cx<T>{v[0].re - v[1].re, v[0].im - v[1].im};
-    } else if (R == 4) {
+    } else if constexpr (R == 4) {
       const cx<T> t0{v[0].re + v[2].re, v[0].im + v[2].im};
       const cx<T> t1{v[0].re - v[2].re, v[0].im - v[2].im};
       const cx<T> t2{v[1].re + v[3].re, v[1].im + v[3].im};
@@ -102,24 +139,64 @@ __device__ void stockham_pass(const cx<T>* in, cx<T>* out, const cx<T>* tw, int 
       V[1] = cx<T>{t1.re + t3.re, t1.im + t3.im};
       V[3] = cx<T>{t1.re - t3.re, t1.im - t3.im};
     } else {
-      const int st = N / R;
+      // odd R: terms r and R - r together, V[s] and V[R - s] from the cosine
+      // sums of v_r + v_{R-r} and the sine sums of v_r - v_{R-r}
+      cx<T> sum[H + 1], dif[H + 1];
+      V[0] = v[0];
 #pragma unroll
-      for (int s = 0; s < R; ++s) {
-        cx<T> acc = v[0];
+      for (int r = 1; r <= H; ++r) {
+        sum[r] = cx<T>{v[r].re + v[R - r].re, v[r].im + v[R - r].im};
+        dif[r] = cx<T>{v[r].re - v[R - r].re, v[r].im - v[R - r].im};
+        V[0].re += sum[r].re;
+        V[0].im += sum[r].im;
+      }
 #pragma unroll
-        for (int r = 1; r < R; ++r) {
-          cx<T> w = tw[((r * s) % R) * st];
-          if (INV) w = cconj(w);
-          const cx<T> y = cmul(v[r], w);
-          acc.re += y.re;
-          acc.im += y.im;
+      for (int s = 1; s <= H; ++s) {
+        cx<T> c = v[0], d{0, 0};
+#pragma unroll
+        for (int r = 1; r <= H; ++r) {
+          const cx<T> w = wr[(r * s) % R];
+          c.re += w.re * sum[r].re;
+          c.im += w.re * sum[r].im;
+          d.re += w.im * dif[r].re;
+          d.im += w.im * dif[r].im;
         }
-        V[s] = acc;
+        V[s] = cx<T>{c.re - d.im, c.im + d.re};
+        V[R - s] = cx<T>{c.re + d.im, c.im - d.re};
       }
     }
-    const int base = (j / Ns) * Ns * R + k;
+    const int base = jq * Ns * R + k;
 #pragma unroll
     for (int r = 0; r < R; ++r) o[base + r * Ns] = V[r];
+  }
+}
+
+// The same pass for any radix R (a prime above 13): one thread per output,
+//   out[(j / Ns) Ns R + k + s Ns] = sum_r in[j + r N/R] w^(r (k N/(Ns R) + s N/R)).
+template <typename T, bool INV>
+__device__ void general_pass(const cx<T>* in, cx<T>* out, const cx<T>* tw, int N, int R, int Ns, Div dN, Div dNs,
+                             Div dnb, int NP) {
+  const int nb = N / R;
+  const int tws = dNs.quot(nb);
+  const int SP = N + 1;
+  for (int idx = threadIdx.x; idx < NP * N; idx += blockDim.x) {
+    const int p = dN.quot(idx);
+    const int e = idx - p * N;
+    const int s = dnb.quot(e), j = e - s * nb;
+    const int jq = dNs.quot(j), k = j - jq * Ns;
+    const cx<T>* a = in + p * SP + j;
+    const int step = k * tws + s * nb;  // below N: k tws < nb and s < R
+    cx<T> acc = a[0];
+    int t = 0;
+    for (int r = 1; r < R; ++r) {
+      t += step;
+      t -= t >= N ? N : 0;
+      const cx<T> x = a[r * nb], w = tw[t];
+      const T wi = INV ? -w.im : w.im;
+      acc.re += x.re * w.re - x.im * wi;
+      acc.im += x.re * wi + x.im * w.re;
+    }
+    out[p * SP + jq * Ns * R + k + s * Ns] = acc;
   }
 }
 
@@ -130,14 +207,16 @@ __device__ cx<T>* run_passes(cx<T>* b0, cx<T>* b1, const cx<T>* tw, const FftPla
   int Ns = 1;
   for (int s = 0; s < plan.nf; ++s) {
     const int R = plan.fac[s];
+    const Div dNs = plan.dNs[s], dnb = plan.dnb[s];
     switch (R) {
-      case 2: stockham_pass<T, INV, 2>(in, out, tw, plan.N, Ns, NP); break;
-      case 3: stockham_pass<T, INV, 3>(in, out, tw, plan.N, Ns, NP); break;
-      case 4: stockham_pass<T, INV, 4>(in, out, tw, plan.N, Ns, NP); break;
-      case 5: stockham_pass<T, INV, 5>(in, out, tw, plan.N, Ns, NP); break;
-      case 7: stockham_pass<T, INV, 7>(in, out, tw, plan.N, Ns, NP); break;
-      case 11: stockham_pass<T, INV, 11>(in, out, tw, plan.N, Ns, NP); break;
-      default: stockham_pass<T, INV, 13>(in, out, tw, plan.N, Ns, NP); break;
+      case 2: stockham_pass<T, INV, 2>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 3: stockham_pass<T, INV, 3>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 4: stockham_pass<T, INV, 4>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 5: stockham_pass<T, INV, 5>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 7: stockham_pass<T, INV, 7>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 11: stockham_pass<T, INV, 11>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      case 13: stockham_pass<T, INV, 13>(in, out, tw, plan.N, Ns, dNs, dnb, NP); break;
+      default: general_pass<T, INV>(in, out, tw, plan.N, R, Ns, plan.dN, dNs, dnb, NP); break;
     }
     __syncthreads();
     cx<T>* t = in;
@@ -153,7 +232,7 @@ __device__ cx<T>* run_passes(cx<T>* b0, cx<T>* b1, const cx<T>* tw, const FftPla
 // DFT whose error is far below the FP32 rounding of the result).
 template <typename T, typename C>
 __global__ __launch_bounds__(256) void fft_r2c_kernel(const T* __restrict__ X, cx<T>* __restrict__ Xb, int64_t ntubes,
-                                                      FftPlan plan, int NP) {
+                                                      FftPlan plan, int NP, Div dNP) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = plan.N;
   cx<C>* tw = reinterpret_cast<cx<C>*>(smem);
@@ -165,17 +244,24 @@ __global__ __launch_bounds__(256) void fft_r2c_kernel(const T* __restrict__ X, c
   const int ntw = (int)min((int64_t)2 * NP, ntubes - t0);
   const T* src = X + t0 * N;
   const int total = ntw * N;
-  for (int g = threadIdx.x; g < 2 * NP * N; g += blockDim.x) {
-    const int tube = g / N, t = g - tube * N;
-    const C v = (g < total) ? (C)src[g] : (C)0;
-    C* dst = reinterpret_cast<C*>(&b0[(tube >> 1) * SP + t]);
-    dst[tube & 1] = v;
+  for (int g0 = threadIdx.x; g0 < 2 * NP * N; g0 += 8 * 256) {
+    T v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = src[min(g0 + u * 256, total - 1)];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int g = g0 + u * 256;
+      if (g >= 2 * NP * N) break;
+      const int tube = plan.dN.quot(g), t = g - tube * N;
+      C* dst = reinterpret_cast<C*>(&b0[(tube >> 1) * SP + t]);
+      dst[tube & 1] = g < total ? (C)v[u] : (C)0;
+    }
   }
   __syncthreads();
   const cx<C>* Z = run_passes<C, false>(b0, b1, tw, plan, NP);
   const int F = N / 2 + 1;
   for (int idx = threadIdx.x; idx < F * 2 * NP; idx += blockDim.x) {
-    const int f = idx / (2 * NP), tube = idx - f * 2 * NP;
+    const int f = dNP.quot(idx >> 1), tube = idx - f * 2 * NP;
     if (tube >= ntw) continue;
     const int p = tube >> 1;
     const cx<C> zf = Z[p * SP + f];
@@ -194,7 +280,8 @@ __global__ __launch_bounds__(256) void fft_r2c_kernel(const T* __restrict__ X, c
 
 template <typename T, typename C>
 __global__ __launch_bounds__(256) void fft_c2r_kernel(const cx<T>* __restrict__ Xb, int64_t slice_stride,
-                                                      T* __restrict__ X, int64_t ntubes, FftPlan plan, int NP) {
+                                                      T* __restrict__ X, int64_t ntubes, FftPlan plan, int NP,
+                                                      Div dNP) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int N = plan.N;
   cx<C>* tw = reinterpret_cast<cx<C>*>(smem);
@@ -205,24 +292,31 @@ __global__ __launch_bounds__(256) void fft_c2r_kernel(const cx<T>* __restrict__ 
   const int64_t t0 = (int64_t)blockIdx.x * 2 * NP;
   const int ntw = (int)min((int64_t)2 * NP, ntubes - t0);
   const int F = N / 2 + 1;
-  for (int idx = threadIdx.x; idx < F * NP; idx += blockDim.x) {
-    const int f = idx / NP, p = idx - f * NP;
-    const int ta = 2 * p, tb = 2 * p + 1;
-    cx<C> a{0, 0}, b{0, 0};
-    if (ta < ntw) {
-      const cx<T> v = Xb[(int64_t)f * slice_stride + t0 + ta];
-      a = cx<C>{(C)v.re, (C)v.im};
+  for (int i0 = threadIdx.x; i0 < F * NP; i0 += 4 * 256) {
+    cx<T> va[4], vb[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = min(i0 + u * 256, F * NP - 1);
+      const int f = dNP.quot(idx), p = idx - f * NP;
+      const cx<T>* src = Xb + (int64_t)f * slice_stride + t0;
+      va[u] = src[min(2 * p, ntw - 1)];
+      vb[u] = src[min(2 * p + 1, ntw - 1)];
     }
-    if (tb < ntw) {
-      const cx<T> v = Xb[(int64_t)f * slice_stride + t0 + tb];
-      b = cx<C>{(C)v.re, (C)v.im};
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int idx = i0 + u * 256;
+      if (idx >= F * NP) break;
+      const int f = dNP.quot(idx), p = idx - f * NP;
+      cx<C> a{0, 0}, b{0, 0};
+      if (2 * p < ntw) a = cx<C>{(C)va[u].re, (C)va[u].im};
+      if (2 * p + 1 < ntw) b = cx<C>{(C)vb[u].re, (C)vb[u].im};
+      if (f == 0 || 2 * f == N) {
+        a.im = 0;
+        b.im = 0;
+      }
+      b0[p * SP + f] = cx<C>{a.re - b.im, a.im + b.re};
+      if (f > 0 && 2 * f != N) b0[p * SP + (N - f)] = cx<C>{a.re + b.im, b.re - a.im};
     }
-    if (f == 0 || 2 * f == N) {
-      a.im = 0;
-      b.im = 0;
-    }
-    b0[p * SP + f] = cx<C>{a.re - b.im, a.im + b.re};
-    if (f > 0 && 2 * f != N) b0[p * SP + (N - f)] = cx<C>{a.re + b.im, b.re - a.im};
   }
   __syncthreads();
   const cx<C>* Z = run_passes<C, true>(b0, b1, tw, plan, NP);
@@ -230,13 +324,13 @@ __global__ __launch_bounds__(256) void fft_c2r_kernel(const cx<T>* __restrict__ 
   const int total = ntw * N;
   T* dst = X + t0 * N;
   for (int g = threadIdx.x; g < total; g += blockDim.x) {
-    const int tube = g / N, t = g - tube * N;
+    const int tube = plan.dN.quot(g), t = g - tube * N;
     const cx<C> z = Z[(tube >> 1) * SP + t];
     dst[g] = (T)(((tube & 1) ? z.im : z.re) * invN);
   }
 }
 
-// Direct DFT for lengths with a prime factor above 13: one thread per output.
+// Direct DFT for lengths beyond LDS: one thread per output.
 template <typename T>
 __global__ void dft_r2c_direct(const T* X, cx<T>* Xb, int64_t ntubes, int N) {
   const int F = N / 2 + 1;
@@ -285,36 +379,36 @@ static int pick_np(int N) {
 template <typename T>
 static hipError_t r2c_t(const void* X, void* Xb, int64_t ntubes, int n3, hipStream_t s) {
   if (ntubes <= 0) return hipSuccess;
-  FftPlan plan = make_plan(n3);
   const int NP = pick_np<double>(n3);
-  if (plan.direct || NP < 1) {
+  if (NP < 1) {
     const int64_t total = ntubes * (n3 / 2 + 1);
     hipLaunchKernelGGL(dft_r2c_direct<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (const T*)X,
                        (cx<T>*)Xb, ntubes, n3);
     return hipGetLastError();
   }
+  const FftPlan plan = make_plan(n3);
   const int64_t nblk = (ntubes + 2 * NP - 1) / (2 * NP);
   const size_t sm = (size_t)(n3 + 2 * NP * (n3 + 1)) * sizeof(cx<double>);
   hipLaunchKernelGGL((fft_r2c_kernel<T, double>), dim3((unsigned)nblk), dim3(256), sm, s, (const T*)X, (cx<T>*)Xb,
-                     ntubes, plan, NP);
+                     ntubes, plan, NP, make_div(NP));
   return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t c2r_t(const void* Xb, int64_t stride, void* X, int64_t ntubes, int n3, hipStream_t s) {
   if (ntubes <= 0) return hipSuccess;
-  FftPlan plan = make_plan(n3);
   const int NP = pick_np<double>(n3);
-  if (plan.direct || NP < 1) {
+  if (NP < 1) {
     const int64_t total = ntubes * n3;
     hipLaunchKernelGGL(dft_c2r_direct<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
                        (const cx<T>*)Xb, stride, (T*)X, ntubes, n3);
     return hipGetLastError();
   }
+  const FftPlan plan = make_plan(n3);
   const int64_t nblk = (ntubes + 2 * NP - 1) / (2 * NP);
   const size_t sm = (size_t)(n3 + 2 * NP * (n3 + 1)) * sizeof(cx<double>);
   hipLaunchKernelGGL((fft_c2r_kernel<T, double>), dim3((unsigned)nblk), dim3(256), sm, s, (const cx<T>*)Xb, stride,
-                     (T*)X, ntubes, plan, NP);
+                     (T*)X, ntubes, plan, NP, make_div(NP));
   return hipGetLastError();
 }
 
