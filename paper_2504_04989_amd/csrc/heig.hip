@@ -1044,7 +1044,7 @@ constexpr int INVIT_B = 8;
 // to ||T|| in [1, 2).
 __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, unsigned char* scratch, size_t per_slice,
                                                         const double* __restrict__ lambda, cx<double>* Wout, int* info,
-                                                        double vfloor_rel) {
+                                                        double vfloor_rel, const int* __restrict__ nvec) {
   extern __shared__ __align__(16) unsigned char smem[];
   // Rows go in batches of B: a batch's operands are read from LDS together, so
   // the chain waits for LDS once per batch.  The rows are padded to whole batches
@@ -1080,6 +1080,10 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
   }
   __syncthreads();
   if (!act) return;  // (one wave, no barrier below)
+  if (nvec && t >= nvec[f]) {  // not wanted
+    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{0.0, 0.0};
+    return;
+  }
   if (tnorm == 0.0) {  // the zero matrix: unit vectors
     for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{i == t ? 1.0 : 0.0, 0.0};
     return;
@@ -1201,7 +1205,8 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
 // gap) of an eigenvector.  A slice without clusters returns at once.
 __global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
                                                            const double* __restrict__ lambda, cx<double>* Wout,
-                                                           int* info, double vfloor_rel, int lds_cols) {
+                                                           int* info, double vfloor_rel, const int* __restrict__ nvec,
+                                                           int lds_cols) {
   extern __shared__ __align__(16) unsigned char smem[];
   double* lam = reinterpret_cast<double*>(smem);  // k
   double* coef = lam + k;                         // k
@@ -1222,11 +1227,12 @@ __global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigne
   const double ortol = INVIT_ORTOL * tn;
   const double vfloor = vfloor_rel > 0.0 ? vfloor_rel * lam[0] : -1e300;
   bool any = false;
-  for (int t = 1 + tid; t < k; t += 256) any |= lam[t - 1] - lam[t] < ortol;
+  const int nv = nvec ? nvec[f] : k;
+  for (int t = 1 + tid; t < nv; t += 256) any |= lam[t - 1] - lam[t] < ortol;
   if (!__syncthreads_or(any)) return;
-  for (int t0 = 0; t0 + 1 < k;) {
+  for (int t0 = 0; t0 + 1 < nv;) {
     int t1 = t0 + 1;
-    while (t1 < k && lam[t1 - 1] - lam[t1] < ortol && (!(vfloor_rel > 0.0) || lam[t1] > vfloor)) ++t1;
+    while (t1 < nv && lam[t1 - 1] - lam[t1] < ortol && (!(vfloor_rel > 0.0) || lam[t1] > vfloor)) ++t1;
     const int n = t1 - t0;
     const bool in_lds = n <= lds_cols;
     auto member = [&](int c, int i) { return in_lds ? buf[(size_t)c * m + i] : W[(int64_t)i * k + t0 + c].re; };
@@ -1445,7 +1451,7 @@ __global__ __launch_bounds__(256) void heig_backxf2_kernel(int m, int k, unsigne
 
 hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, int k, int batch, double* lambda,
                      double* W, void* scratch, int* info, hipStream_t s, int stages, bool upper_only,
-                     double vfloor_rel) {
+                     double vfloor_rel, const int* nvec) {
   if (batch <= 0) return hipSuccess;
   if (m > 1024 || k > m || k < 1) return hipErrorInvalidValue;
   static bool attr_set = false;
@@ -1581,13 +1587,13 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
                                  (int)lds_cu)) != hipSuccess)
       return e;
     hipLaunchKernelGGL(heig_invit_kernel, dim3(batch, (k + nl - 1) / nl), dim3(64), sm3, s, m, k, nl, sc, per, lambda,
-                       (cx<double>*)W, info, vfloor_rel);
+                       (cx<double>*)W, info, vfloor_rel, nvec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k > 1) {
       const size_t base = (size_t)(2 * k + m) * sizeof(double);
       const int cols = (int)std::min<size_t>(k, (60 * 1024 - base) / (m * sizeof(double)));
       hipLaunchKernelGGL(heig_cluster_kernel, dim3(batch), dim3(256), base + (size_t)cols * m * sizeof(double), s, m, k,
-                         sc, per, lambda, (cx<double>*)W, info, vfloor_rel, cols);
+                         sc, per, lambda, (cx<double>*)W, info, vfloor_rel, nvec, cols);
       if ((e = hipGetLastError()) != hipSuccess) return e;
     }
   }

@@ -137,10 +137,11 @@ size_t heig_scratch_bytes(int m, int k);
 // upper_only: only the entries on and above the diagonal of the summed
 // partials are valid (the matrix is taken as their Hermitian extension).
 // vfloor_rel > 0: eigenvalues lambda_j <= vfloor_rel * lambda_0 get a zero
-// vector instead of an inverse iteration.
+// vector instead of an inverse iteration.  nvec (device, one per slice): so do
+// the eigenvalues from nvec[f] on.
 hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, int k, int batch, double* lambda,
                      double* W, void* scratch, int* info, hipStream_t s, int stages = HEIG_ALL,
-                     bool upper_only = false, double vfloor_rel = 0.0);
+                     bool upper_only = false, double vfloor_rel = 0.0, const int* nvec = nullptr);
 
 // Lift helpers.
 // Wout (batch x m x k, dtype t) = W * diag(scale) where scale = sqrt(lambda)
@@ -174,10 +175,6 @@ hipError_t triu_store(const double* part, int nsum, int64_t part_stride, int r, 
 // C (n elements of dtype t) = mask ? M : X (X == nullptr: 0).
 hipError_t masked_merge(const void* M, const unsigned char* mask, const void* X, void* C, int64_t n, DType t,
                         hipStream_t s);
-// Second pass of the FP64 small SVD: the number J of the first pass's top-k
-// eigenpairs (lam1, W1: m x k per slice) kept per slice, with W1m = W1 whose
-// columns from J on are cleared; and the merge of the kept pairs with the
-// second pass's (lam2, W2) into lambda and W (m x k).
 // Adjoint through the rank-k truncation: per slice, S = N + N^H from
 // M (m x m, FP64 complex) and the descending eigenvalues lambda (m):
 // S_xy = (M_xy + conj(M_yx)) / (lambda_min(x,y) - lambda_max(x,y)) when
@@ -185,8 +182,11 @@ hipError_t masked_merge(const void* M, const unsigned char* mask, const void* X,
 // rel_tol * lambda_0 gives 0 there and counts in info[INFO_TIE].
 hipError_t gap_weights(const void* M, const double* lambda, int m, int k, int batch, double rel_tol, void* S,
                        int* info, hipStream_t s);
-hipError_t tail_split(const double* lam1, const void* W1, void* W1m, int m, int k, int batch, double tau,
-                      double min_ratio, int* J, hipStream_t s);
+// Second pass of the FP64 small SVD: the number J of the first pass's top-k
+// eigenpairs that are kept per slice, from its eigenvalues; and the merge of the
+// kept pairs (lam1, W1: m x k per slice, W1 zero from column J on) with the
+// second pass's (lam2, W2) into lambda and W (m x k).
+hipError_t tail_split(const double* lam1, int k, int batch, double tau, double min_ratio, int* J, hipStream_t s);
 hipError_t tail_merge(const double* lam1, const void* W1, const double* lam2, const void* W2, const int* J, int m,
                       int k, int batch, double* lam, void* W, hipStream_t s);
 hipError_t zero_info(int* info, hipStream_t s);

@@ -311,37 +311,21 @@ hipError_t gap_weights(const void* M, const double* lambda, int m, int k, int ba
 // Second pass of the FP64 small SVD.  tail_split: per slice, the number J of
 // leading eigenpairs of the first pass that are kept: the largest J < k with
 // lambda_{J-1} >= tau lambda_0 and lambda_{J-1} / lambda_J >= min_ratio (no
-// such J: J = k, the first pass is kept whole); W1m = W1 with the columns
-// from J on cleared.
-__global__ void tail_split_kernel(const double* __restrict__ lam1, const cx<double>* __restrict__ W1,
-                                  cx<double>* __restrict__ W1m, int m, int k, double tau, double min_ratio,
-                                  int* __restrict__ J) {
-  __shared__ int js;
-  const int f = blockIdx.x;
-  if (threadIdx.x == 0) {
-    const double* l = lam1 + (int64_t)f * k;
-    int best = 0;
-    for (int j = 1; j < k; ++j) {
-      const double a = l[j - 1], bj = l[j];
-      if (a >= tau * l[0] && (bj <= 0.0 || a >= min_ratio * bj)) best = j;
-    }
-    if (best == 0) best = k;
-    js = best;
-    J[f] = best;
+// such J: J = k, the first pass is kept whole).
+__global__ __launch_bounds__(64) void tail_split_kernel(const double* __restrict__ lam1, int k, double tau,
+                                                        double min_ratio, int* __restrict__ J) {
+  const double* l = lam1 + (int64_t)blockIdx.x * k;
+  int best = 0;
+  for (int j = 1 + threadIdx.x; j < k; j += 64) {
+    const double a = l[j - 1], bj = l[j];
+    if (a >= tau * l[0] && (bj <= 0.0 || a >= min_ratio * bj)) best = j;
   }
-  __syncthreads();
-  const int jf = js;
-  const int64_t per = (int64_t)m * k;
-  for (int64_t e = threadIdx.x; e < per; e += blockDim.x) {
-    const int c = (int)(e % k);
-    W1m[(int64_t)f * per + e] = c < jf ? W1[(int64_t)f * per + e] : cx<double>{0.0, 0.0};
-  }
+  for (int off = 32; off > 0; off >>= 1) best = max(best, __shfl_xor(best, off, 64));
+  if (threadIdx.x == 0) J[blockIdx.x] = best == 0 ? k : best;
 }
-hipError_t tail_split(const double* lam1, const void* W1, void* W1m, int m, int k, int batch, double tau,
-                      double min_ratio, int* J, hipStream_t s) {
+hipError_t tail_split(const double* lam1, int k, int batch, double tau, double min_ratio, int* J, hipStream_t s) {
   if (batch <= 0) return hipSuccess;
-  hipLaunchKernelGGL(tail_split_kernel, dim3(batch), dim3(256), 0, s, lam1, (const cx<double>*)W1, (cx<double>*)W1m,
-                     m, k, tau, min_ratio, J);
+  hipLaunchKernelGGL(tail_split_kernel, dim3(batch), dim3(64), 0, s, lam1, k, tau, min_ratio, J);
   return hipGetLastError();
 }
 

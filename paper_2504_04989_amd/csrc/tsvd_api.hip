@@ -60,7 +60,7 @@ struct Plan {
   // workspace offsets (bytes)
   size_t o_canon, o_rout, o_xp;
   size_t o_cbuf, o_xbuf, o_uo, o_so, o_vo;  // completion: C^(n), X^(n) and the factors of L
-  size_t o_lam1, o_w1, o_w1m, o_p, o_t1, o_lam2, o_w2, o_rk, o_split;  // FP64 small SVD, second pass
+  size_t o_lam1, o_w1, o_p, o_t1, o_lam2, o_w2, o_rk, o_split;  // FP64 small SVD, second pass
   size_t o_omsp;  // the spatial test tensor drawn from the seed (n2 x b x n3, storage type)
   size_t o_vr, o_sr;  // truncated basis: spatial V and S of its Ritz step (scratch outputs)
   // adjoint through the rank-k truncation: all eigenpairs of C C^H, four
@@ -299,7 +299,6 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
   const bool pass2 = need_svd && p->dt == DT_F64;
   p->o_lam1 = take(pass2 ? (size_t)F * ks * 8 : 0);
   p->o_w1 = take(pass2 ? (size_t)F * m * ks * 16 : 0);
-  p->o_w1m = take(pass2 ? (size_t)F * m * ks * 16 : 0);
   p->o_p = take(pass2 ? (size_t)F * n2 * ks * 16 : 0);
   p->o_t1 = take(pass2 ? (size_t)F * n2 * m * 16 : 0);
   p->o_lam2 = take(pass2 ? (size_t)F * ks * 8 : 0);
@@ -970,23 +969,23 @@ int svd_and_lift(const Ctx& c, void* U, void* S, void* V) {
     // FP64: the eigenvalues of the Gram carry an absolute error of order
     // m u lambda_0, which leaves sigma_j below about sqrt(m u) sigma_0
     // unresolved.  The first pass keeps its J leading eigenpairs (above
-    // 1e-9 lambda_0 and a gap); the second pass projects them out of C^H,
-    // T1 = T (I - W_J W_J^H), and takes the top eigenpairs of T1^H T1, whose
-    // absolute error scales with the much smaller norm of the rest; they are
-    // projected off W_J once more and fill the columns from J on.
-    // (no vectors are formed below half that level: tail_split keeps none of them)
+    // 1e-9 lambda_0 and a gap; all k without such a gap); the second pass
+    // projects them out of C^H, T1 = T (I - W_J W_J^H), and takes the top
+    // eigenpairs of T1^H T1, whose absolute error scales with the much smaller
+    // norm of the rest; they are projected off W_J once more and fill the columns
+    // from J on.  J follows from the eigenvalues, so the first pass forms the
+    // J vectors alone (W1 is zero from column J on).
     double* lam1 = c.at<double>(p.o_lam1);
     double* W1 = c.at<double>(p.o_w1);
+    int* J = c.at<int>(p.o_split);
     for (const auto& sc : stage_cls) {
+      if (sc[0] == HEIG_INVIT) {
+        Timed tm_(K_MISC, c.s);
+        HIPCHK(tail_split(lam1, (int)p.k, (int)p.F, 1e-9, 1.5, J, c.s));
+      }
       Timed tm_(sc[1], c.s);
       HIPCHK(heig_topk(part, nsum_g, p.F * p.m * p.m, (int)p.m, (int)p.k, (int)p.F, lam1, W1, c.at(p.o_heig),
-                       c.info(), c.s, sc[0], false, 0.5e-9));
-    }
-    int* J = c.at<int>(p.o_split);
-    void* W1m = c.at(p.o_w1m);
-    {
-      Timed tm_(K_MISC, c.s);
-      HIPCHK(tail_split(lam1, W1, W1m, (int)p.m, (int)p.k, (int)p.F, 1e-9, 1.5, J, c.s));
+                       c.info(), c.s, sc[0], false, 0.0, J));
     }
     auto z64 = [&](const void* A, int64_t lda, int64_t sa, bool ac, const void* B, int64_t ldb, int64_t sb, bool bc,
                    void* C, int64_t ldc, int64_t sc, int M, int N, int K, double alpha, double beta) -> int {
@@ -1019,11 +1018,11 @@ int svd_and_lift(const Ctx& c, void* U, void* S, void* V) {
     const int im = (int)p.m, ik = (int)p.k, in2 = (int)p.n2;
     void* P = c.at(p.o_p);
     void* T1 = c.at(p.o_t1);
-    // P = T W1m (n2 x k); T1 = T - P W1m^H (n2 x m)
-    if ((r = z64(T, p.m, p.n2 * p.m, false, W1m, p.k, p.m * p.k, false, P, p.k, p.n2 * p.k, in2, ik, im, 1.0, 0.0)))
+    // P = T W1 (n2 x k); T1 = T - P W1^H (n2 x m)
+    if ((r = z64(T, p.m, p.n2 * p.m, false, W1, p.k, p.m * p.k, false, P, p.k, p.n2 * p.k, in2, ik, im, 1.0, 0.0)))
       return r;
     HIPCHK(hipMemcpyAsync(T1, T, (size_t)p.F * p.n2 * p.m * 16, hipMemcpyDeviceToDevice, c.s));
-    if ((r = z64(P, p.k, p.n2 * p.k, false, W1m, p.k, p.m * p.k, true, T1, p.m, p.n2 * p.m, in2, im, ik, -1.0, 1.0)))
+    if ((r = z64(P, p.k, p.n2 * p.k, false, W1, p.k, p.m * p.k, true, T1, p.m, p.n2 * p.m, in2, im, ik, -1.0, 1.0)))
       return r;
     int nsum2 = 1;
     r = inner_products(c, T1, p.m, im, T1, p.m, im, p.n2, p.n2 * p.m, p.n2 * p.m, p.nsplit_g, p.kchunk_g, part,
@@ -1036,11 +1035,11 @@ int svd_and_lift(const Ctx& c, void* U, void* S, void* V) {
       HIPCHK(heig_topk(part, nsum2, p.F * p.m * p.m, im, ik, (int)p.F, lam2, W2, c.at(p.o_heig), c.info(), c.s,
                        sc[0], false));
     }
-    // W2 -= W1m (W1m^H W2)
+    // W2 -= W1 (W1^H W2)
     void* Rk = c.at(p.o_rk);
-    if ((r = z64(W1m, p.k, p.m * p.k, true, W2, p.k, p.m * p.k, false, Rk, p.k, p.k * p.k, ik, ik, im, 1.0, 0.0)))
+    if ((r = z64(W1, p.k, p.m * p.k, true, W2, p.k, p.m * p.k, false, Rk, p.k, p.k * p.k, ik, ik, im, 1.0, 0.0)))
       return r;
-    if ((r = z64(W1m, p.k, p.m * p.k, false, Rk, p.k, p.k * p.k, false, W2, p.k, p.m * p.k, im, ik, ik, -1.0, 1.0)))
+    if ((r = z64(W1, p.k, p.m * p.k, false, Rk, p.k, p.k * p.k, false, W2, p.k, p.m * p.k, im, ik, ik, -1.0, 1.0)))
       return r;
     {
       Timed tm_(K_MISC, c.s);
