@@ -1034,68 +1034,24 @@ __device__ __forceinline__ double hash_uniform(uint32_t a, uint32_t b) {
 constexpr double INVIT_ORTOL = 1e-9;
 constexpr int INVIT_B = 8;
 
-// One eigenvector per lane, nl of them per one-wave workgroup: the pivoted LU of
-// T - lambda I and the solves are chains of m dependent steps, and the chains
-// of all lanes cost what one did when a wave walked one.  Bound: the latency of
-// those chains (about 4 m steps).  The reciprocal pivots, multipliers and
-// iterate of the lanes are in LDS (24 m nl bytes; fetched from memory instead,
-// the chains ran at a third of the speed); the entry right of the pivot follows
-// from T, the multipliers and the row-swap bits.  T is scaled by a power of two
-// to ||T|| in [1, 2).
-__global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, unsigned char* scratch, size_t per_slice,
-                                                        const double* __restrict__ lambda, cx<double>* Wout, int* info,
-                                                        double vfloor_rel, const int* __restrict__ nvec) {
-  extern __shared__ __align__(16) unsigned char smem[];
-  // Rows go in batches of B: a batch's operands are read from LDS together, so
-  // the chain waits for LDS once per batch.  The rows are padded to whole batches
-  // by uncoupled ones, so that no row takes a branch.
-  constexpr int B = INVIT_B;
-  const int mp = (m + B - 1) / B * B;
-  double* d = reinterpret_cast<double*>(smem);                // mp + 1
-  double* e = d + mp + 1;                                     // mp + 1
-  double* R = e + mp + 1;                                     // mp x nl: 1 / pivot
-  double* Mu = R + mp * nl;                                   // mp x nl: multipliers
-  double* Z = Mu + mp * nl;                                   // mp x nl: the iterate
-  unsigned char* swaps = reinterpret_cast<unsigned char*>(Z + mp * nl);  // mp / B x 64: swap bits of a batch
-  const int f = blockIdx.x, lane = threadIdx.x;
-  HeigView hv = heig_view(scratch, per_slice, f, m);
-  for (int i = lane; i <= mp; i += 64) {
-    d[i] = i < m ? hv.d[i] : 4.0;
-    e[i] = i + 1 < m ? hv.e[i] : 0.0;
-  }
-  __syncthreads();
-  double gl, gu, pivmin, tnorm;
-  tri_bounds(d, e, m, &gl, &gu, &pivmin, &tnorm);
-  const int t = blockIdx.y * nl + lane;
-  const double* lam = lambda + (int64_t)f * k;
-  cx<double>* W = Wout + (int64_t)f * m * k + t;
-  const bool act = lane < nl && t < k;
-  int ex = 0;
-  (void)frexp(tnorm, &ex);
-  const double up = isfinite(tnorm) && tnorm > 0.0 ? ldexp(1.0, 1 - ex) : 1.0;
-  __syncthreads();
-  for (int i = lane; i < m; i += 64) {
-    d[i] *= up;  // (the padding rows keep 4: off any eigenvalue)
-    e[i] *= up;
-  }
-  __syncthreads();
-  if (!act) return;  // (one wave, no barrier below)
-  if (nvec && t >= nvec[f]) {  // not wanted
-    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{0.0, 0.0};
-    return;
-  }
-  if (tnorm == 0.0) {  // the zero matrix: unit vectors
-    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{i == t ? 1.0 : 0.0, 0.0};
-    return;
-  }
-  const double lv = lam[t] * up;
-  const double eps = 2.220446049250313e-16;
-  R += lane;
-  Mu += lane;
-  Z += lane;
-  swaps += lane;
+// One lane's shifted solves with T (in LDS, scaled to ||T|| in [1, 2)): the pivoted
+// LU of T - lambda I and its two substitutions, chains of mp dependent steps.
+// Rows go in batches of INVIT_B: a batch's operands are read from LDS together,
+// so the chain waits for LDS once per batch.  The rows are padded to whole batches
+// by uncoupled ones, so that no row takes a branch.  The lanes' arrays are
+// interleaved with stride nl (the swap bits with ss).  The entry right of the
+// pivot follows from T, the multipliers and the row-swap bits.
+struct ShiftedT {
+  const double *d, *e;   // mp + 1 each
+  double *R, *Mu, *Z;    // mp each: 1 / pivot, multipliers, the iterate
+  unsigned char* swaps;  // mp / INVIT_B: swap bits of a batch
+  int mp, nl, ss;
+  double lv;
+
   // LU with row interchanges; pivots are kept at or above eps in modulus
-  {
+  __device__ __forceinline__ void factor() const {
+    constexpr int B = INVIT_B;
+    const double eps = 2.220446049250313e-16;
     double pc = d[0] - lv, qc = e[0];
     for (int i0 = 0; i0 < mp; i0 += B) {
       double dn[B], eb[B + 1];
@@ -1122,26 +1078,47 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
         Mu[(i0 + u) * nl] = mu;
         bits |= (unsigned)sw << u;
       }
-      swaps[(i0 / B) * 64] = (unsigned char)bits;
+      swaps[(i0 / B) * ss] = (unsigned char)bits;
     }
   }
-  // Back substitution: the entries right of the pivot are (d_{i+1} - lambda,
-  // e_{i+1}) in a swapped row, else e_i, or -mu_{i-1} e_i behind a swapped row.
-  // FIRST: of a random right-hand side (zero in the padding rows).  Returns ||z||^2.
-  auto back = [&](auto first) {
-    constexpr bool FIRST = decltype(first)::value;
+
+  // forward elimination of Z * scale, in place
+  __device__ __forceinline__ void forward(double scale) const {
+    constexpr int B = INVIT_B;
+    double zc = Z[0] * scale;
+    for (int i0 = 0; i0 < mp; i0 += B) {
+      const unsigned bits = swaps[(i0 / B) * ss];
+      double zb[B], mb[B];
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        zb[u] = Z[(u < B - 1 ? i0 + u + 1 : min(i0 + B, mp - 1)) * nl] * scale;
+        mb[u] = Mu[(i0 + u) * nl];
+      }
+#pragma unroll
+      for (int u = 0; u < B; ++u) {
+        const bool sw = (bits >> u) & 1u;
+        const double x = sw ? zb[u] : zc, y = sw ? zc : zb[u];
+        Z[(i0 + u) * nl] = x;  // (the last row neither swaps nor feeds another)
+        zc = fma(-mb[u], x, y);
+      }
+    }
+  }
+
+  // Back substitution into Z, of Z or of rhs(i): the entries right of the pivot
+  // are (d_{i+1} - lambda, e_{i+1}) in a swapped row, else e_i, or -mu_{i-1} e_i
+  // behind a swapped row.  Returns ||z||^2.
+  template <typename Rhs>
+  __device__ __forceinline__ double back(Rhs rhs) const {
+    constexpr int B = INVIT_B;
     double z1 = 0.0, z2 = 0.0, nrm = 0.0;
     for (int i0 = mp - B; i0 >= 0; i0 -= B) {
-      const unsigned bits = swaps[(i0 / B) * 64];
-      const unsigned low = i0 > 0 ? swaps[(i0 / B - 1) * 64] >> (B - 1) : 0;  // row i0 - 1 swapped
+      const unsigned bits = swaps[(i0 / B) * ss];
+      const unsigned low = i0 > 0 ? swaps[(i0 / B - 1) * ss] >> (B - 1) : 0;  // row i0 - 1 swapped
       double cb[B], mb[B], rb[B], db[B], eb[B + 1];
 #pragma unroll
       for (int u = 0; u < B; ++u) {
         const int i = i0 + u;
-        if (FIRST)
-          cb[u] = i < m ? hash_uniform((uint32_t)t, (uint32_t)i) : 0.0;
-        else
-          cb[u] = Z[i * nl];
+        cb[u] = rhs(i);
         mb[u] = Mu[(u > 0 ? i - 1 : max(i - 1, 0)) * nl];
         rb[u] = R[i * nl];
         db[u] = d[i + 1] - lv;
@@ -1161,29 +1138,74 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
       }
     }
     return nrm;
-  };
-  double nrm = back(std::true_type{});
+  }
+  __device__ __forceinline__ double back() const {
+    return back([&](int i) { return Z[i * nl]; });
+  }
+};
+
+// Factor that brings ||T|| into [1, 2).
+__device__ __forceinline__ double unit_scale(double tnorm) {
+  int ex = 0;
+  (void)frexp(tnorm, &ex);
+  return isfinite(tnorm) && tnorm > 0.0 ? ldexp(1.0, 1 - ex) : 1.0;
+}
+
+// One eigenvector per lane, nl of them per one-wave workgroup: the chains of all
+// lanes cost what one did when a wave walked one.  Bound: the latency of those
+// chains (about 4 m steps).  The reciprocal pivots, multipliers and iterate of
+// the lanes are in LDS (24 m nl bytes; fetched from memory instead, the chains
+// ran at a third of the speed).
+__global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, unsigned char* scratch, size_t per_slice,
+                                                        const double* __restrict__ lambda, cx<double>* Wout, int* info,
+                                                        double vfloor_rel, const int* __restrict__ nvec) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int B = INVIT_B;
+  const int mp = (m + B - 1) / B * B;
+  double* d = reinterpret_cast<double*>(smem);                // mp + 1
+  double* e = d + mp + 1;                                     // mp + 1
+  double* R = e + mp + 1;                                     // mp x nl: 1 / pivot
+  double* Mu = R + mp * nl;                                   // mp x nl: multipliers
+  double* Z = Mu + mp * nl;                                   // mp x nl: the iterate
+  unsigned char* swaps = reinterpret_cast<unsigned char*>(Z + mp * nl);  // mp / B x 64: swap bits of a batch
+  const int f = blockIdx.x, lane = threadIdx.x;
+  HeigView hv = heig_view(scratch, per_slice, f, m);
+  for (int i = lane; i <= mp; i += 64) {
+    d[i] = i < m ? hv.d[i] : 4.0;
+    e[i] = i + 1 < m ? hv.e[i] : 0.0;
+  }
+  __syncthreads();
+  double gl, gu, pivmin, tnorm;
+  tri_bounds(d, e, m, &gl, &gu, &pivmin, &tnorm);
+  const int t = blockIdx.y * nl + lane;
+  const double* lam = lambda + (int64_t)f * k;
+  cx<double>* W = Wout + (int64_t)f * m * k + t;
+  const bool act = lane < nl && t < k;
+  const double up = unit_scale(tnorm);
+  __syncthreads();
+  for (int i = lane; i < m; i += 64) {
+    d[i] *= up;  // (the padding rows keep 4: off any eigenvalue)
+    e[i] *= up;
+  }
+  __syncthreads();
+  if (!act) return;  // (one wave, no barrier below)
+  if (nvec && t >= nvec[f]) {  // not wanted
+    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{0.0, 0.0};
+    return;
+  }
+  if (tnorm == 0.0) {  // the zero matrix: unit vectors
+    for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{i == t ? 1.0 : 0.0, 0.0};
+    return;
+  }
+  const double eps = 2.220446049250313e-16;
+  const ShiftedT s{d, e, R + lane, Mu + lane, Z + lane, swaps + lane, mp, nl, 64, lam[t] * up};
+  s.factor();
+  // a random right-hand side (zero in the padding rows)
+  double nrm = s.back([&](int i) { return i < m ? hash_uniform((uint32_t)t, (uint32_t)i) : 0.0; });
   double scale = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0, res = 1.0;
   for (int it = 1; it < 4; ++it) {
-    // forward elimination of the normalised iterate
-    double zc = Z[0] * scale;
-    for (int i0 = 0; i0 < mp; i0 += B) {
-      const unsigned bits = swaps[(i0 / B) * 64];
-      double zb[B], mb[B];
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        zb[u] = Z[(u < B - 1 ? i0 + u + 1 : min(i0 + B, mp - 1)) * nl] * scale;
-        mb[u] = Mu[(i0 + u) * nl];
-      }
-#pragma unroll
-      for (int u = 0; u < B; ++u) {
-        const bool sw = (bits >> u) & 1u;
-        const double x = sw ? zb[u] : zc, y = sw ? zc : zb[u];
-        Z[(i0 + u) * nl] = x;  // (the last row neither swaps nor feeds another)
-        zc = fma(-mb[u], x, y);
-      }
-    }
-    nrm = back(std::false_type{});
+    s.forward(scale);
+    nrm = s.back();
     // the right-hand side had norm 1 (from the second solve on), so the
     // normalised iterate's residual is 1 / ||z||
     scale = nrm > 0.0 ? 1.0 / sqrt(nrm) : 0.0;
@@ -1194,7 +1216,7 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
   const bool floor_out = vfloor_rel > 0.0 && !(lam[t] > vfloor_rel * lam[0]);
   if (!floor_out && !(res <= 1e3 * m * eps)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
 #pragma unroll 4
-  for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{floor_out ? 0.0 : Z[i * nl] * scale, 0.0};
+  for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{floor_out ? 0.0 : s.Z[i * nl] * scale, 0.0};
 }
 
 // Orthogonalisation inside the clusters of close eigenvalues, one workgroup per
@@ -1202,17 +1224,30 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
 // members come out of independent random starts, so they span the cluster's
 // invariant subspace, and a combination of members stays within the cluster's
 // width (below 1e-9 ||T|| per gap, weighted by the members' contamination eps /
-// gap) of an eigenvector.  A slice without clusters returns at once.
+// gap) of an eigenvector.  Where the eigenvalues of a cluster differ by less than
+// their rounding, its members lean towards the same few directions; what
+// Gram-Schmidt leaves of the later ones is short, and rescaling it raises its
+// rounding error.  So each member's residual is measured, and while it is above
+// 16 eps ||T|| the member is solved for and orthogonalised again, up to three
+// times (190 equal eigenvalues of 192: residual 1e-11 ||T|| without, 2e-14 with).
+// A slice without clusters returns at once.
 __global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
                                                            const double* __restrict__ lambda, cx<double>* Wout,
                                                            int* info, double vfloor_rel, const int* __restrict__ nvec,
                                                            int lds_cols) {
   extern __shared__ __align__(16) unsigned char smem[];
+  constexpr int B = INVIT_B;
+  const int mp = (m + B - 1) / B * B;
   double* lam = reinterpret_cast<double*>(smem);  // k
   double* coef = lam + k;                         // k
-  double* cur = coef + k;                         // m: the vector being orthogonalised
-  double* buf = cur + m;                          // lds_cols x m: the cluster's earlier members
-  __shared__ double red[4];
+  double* d = coef + k;                           // mp + 1: T, as in heig_invit_kernel
+  double* e = d + mp + 1;                         // mp + 1
+  double* R = e + mp + 1;                         // mp
+  double* Mu = R + mp;                            // mp
+  double* cur = Mu + mp;                          // mp: the vector being orthogonalised
+  double* buf = cur + mp;                         // lds_cols x m: the cluster's earlier members
+  unsigned char* swaps = reinterpret_cast<unsigned char*>(buf + (size_t)lds_cols * m);  // mp / B
+  __shared__ double red[8];
   const int f = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
   HeigView hv = heig_view(scratch, per_slice, f, m);
   cx<double>* W = Wout + (int64_t)f * m * k;
@@ -1230,6 +1265,13 @@ __global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigne
   const int nv = nvec ? nvec[f] : k;
   for (int t = 1 + tid; t < nv; t += 256) any |= lam[t - 1] - lam[t] < ortol;
   if (!__syncthreads_or(any)) return;
+  const double eps = 2.220446049250313e-16, up = unit_scale(tn);
+  for (int i = tid; i <= mp; i += 256) {
+    d[i] = i < m ? hv.d[i] * up : 4.0;
+    e[i] = i + 1 < m ? hv.e[i] * up : 0.0;
+    if (i < mp) cur[i] = 0.0;
+  }
+  __syncthreads();
   for (int t0 = 0; t0 + 1 < nv;) {
     int t1 = t0 + 1;
     while (t1 < nv && lam[t1 - 1] - lam[t1] < ortol && (!(vfloor_rel > 0.0) || lam[t1] > vfloor)) ++t1;
@@ -1237,33 +1279,55 @@ __global__ __launch_bounds__(256) void heig_cluster_kernel(int m, int k, unsigne
     const bool in_lds = n <= lds_cols;
     auto member = [&](int c, int i) { return in_lds ? buf[(size_t)c * m + i] : W[(int64_t)i * k + t0 + c].re; };
     for (int j = 0; n > 1 && j < n; ++j) {
+      const ShiftedT st{d, e, R, Mu, cur, swaps, mp, 1, 1, lam[t0 + j] * up};
       for (int i = tid; i < m; i += 256) cur[i] = W[(int64_t)i * k + t0 + j].re;
       __syncthreads();
-      for (int pass = 0; pass < 2 && j > 0; ++pass) {
-        for (int c = wv; c < j; c += 4) {
-          double s = 0;
-          for (int i = lane; i < m; i += 64) s = fma(member(c, i), cur[i], s);
-          s = wave_sum(s);
-          if (lane == 0) coef[c] = s;
+      double sc = 0.0;
+      int it = 0;
+      for (;; ++it) {
+        for (int pass = 0; pass < 2 && j > 0; ++pass) {
+          for (int c = wv; c < j; c += 4) {
+            double s = 0;
+            for (int i = lane; i < m; i += 64) s = fma(member(c, i), cur[i], s);
+            s = wave_sum(s);
+            if (lane == 0) coef[c] = s;
+          }
+          __syncthreads();
+          for (int i = tid; i < m; i += 256) {
+            double s = cur[i];
+            for (int c = 0; c < j; ++c) s = fma(-coef[c], member(c, i), s);
+            cur[i] = s;
+          }
+          __syncthreads();
         }
-        __syncthreads();
+        // squared norms of the vector and of (T - lambda) times it
+        cx<double> ss{0.0, 0.0};
         for (int i = tid; i < m; i += 256) {
-          double s = cur[i];
-          for (int c = 0; c < j; ++c) s = fma(-coef[c], member(c, i), s);
-          cur[i] = s;
+          const double x = cur[i];
+          const double y = fma(d[i] - st.lv, x, fma(i > 0 ? e[i - 1] : 0.0, i > 0 ? cur[i - 1] : 0.0,
+                                                    e[i] * (i + 1 < m ? cur[i + 1] : 0.0)));
+          ss.re = fma(x, x, ss.re);
+          ss.im = fma(y, y, ss.im);
+        }
+        ss = block_sum2<4>(ss, red);
+        sc = ss.re > 0 ? 1.0 / sqrt(ss.re) : 0.0;
+        const double res = sqrt(ss.im) * sc;
+        if (sc > 0.0 && res <= 16.0 * eps) break;
+        if (it == 3) {
+          if (tid == 0 && !(sc > 0.0 && res <= 1e3 * m * eps)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
+          break;
+        }
+        if (tid == 0) {
+          if (it == 0) st.factor();
+          st.forward(sc);
+          st.back();
         }
         __syncthreads();
       }
-      double s = 0;
-      for (int i = tid; i < m; i += 256) s = fma(cur[i], cur[i], s);
-      s = block_sum<256>(s, red);
-      // (a member inside the span of the earlier ones would be left without digits)
-      if (tid == 0 && !(s > 1e-14)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
-      const double sc = s > 0 ? 1.0 / sqrt(s) : 0.0;
       for (int i = tid; i < m; i += 256) {
         const double x = cur[i] * sc;
         if (in_lds) buf[(size_t)j * m + i] = x;
-        if (j > 0) W[(int64_t)i * k + t0 + j].re = x;
+        if (j > 0 || it > 0) W[(int64_t)i * k + t0 + j].re = x;
       }
       __syncthreads();
     }
@@ -1590,8 +1654,13 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
                        (cx<double>*)W, info, vfloor_rel, nvec);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (k > 1) {
-      const size_t base = (size_t)(2 * k + m) * sizeof(double);
-      const int cols = (int)std::min<size_t>(k, (60 * 1024 - base) / (m * sizeof(double)));
+      // up to 60 KB of members in LDS beside T, its factors and the coefficients (at most 58)
+      const size_t mp = (size_t)(m + INVIT_B - 1) / INVIT_B * INVIT_B;
+      const size_t base = (2 * k + 2 * (mp + 1) + 3 * mp) * sizeof(double) + mp / INVIT_B;
+      const int cols = (int)std::min<size_t>(k, 60 * 1024 / (m * sizeof(double)));
+      if ((e = hipFuncSetAttribute((const void*)heig_cluster_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                   120 * 1024)) != hipSuccess)
+        return e;
       hipLaunchKernelGGL(heig_cluster_kernel, dim3(batch), dim3(256), base + (size_t)cols * m * sizeof(double), s, m, k,
                          sc, per, lambda, (cx<double>*)W, info, vfloor_rel, nvec, cols);
       if ((e = hipGetLastError()) != hipSuccess) return e;
