@@ -902,7 +902,7 @@ __global__ __launch_bounds__(RES_NT, 1) void heig_trires_kernel(const cx<double>
 }
 
 // ---------------------------------------------------------------------------
-// 2. eigenvalues by multisection (one wave per eigenvalue)
+// 2. eigenvalues by multisection (8, 16 or 64 lanes per eigenvalue)
 // ---------------------------------------------------------------------------
 // Number of eigenvalues of T below x; de holds (d_i, e_{i-1}^2).
 __device__ __forceinline__ int sturm_count(const double2* de, int m, double x, double pivmin) {
@@ -961,7 +961,8 @@ __device__ void tri_bounds(const double* d, const double* e, int m, double* gl, 
 // the eigenvalue.  Bound: the vector issue of m steps per round and wave when
 // there are several waves per SIMD, the latency of that chain otherwise.  More
 // lanes per eigenvalue mean fewer rounds (9 to 10 for L = 64, 13 for 16, 17 for
-// 8) of more waves.
+// 8) of more waves.  Small eigenvalues are resolved relative to themselves; the
+// limit of rounds (an interval 1e-115 of the first) is met by exact zeros only.
 template <int L>
 __global__ __launch_bounds__(256) void heig_bisect_kernel(int m, int k, unsigned char* scratch, size_t per_slice,
                                                           double* __restrict__ lambda_out, int* info) {
@@ -988,10 +989,10 @@ __global__ __launch_bounds__(256) void heig_bisect_kernel(int m, int k, unsigned
   tri_bounds(d, e, m, &lo, &hi, &pivmin, &tnorm);
   const int idx = m - 1 - t;
   const double eps = 2.220446049250313e-16;
+  constexpr int ROUNDS = L >= 64 ? 64 : L >= 16 ? 94 : 121;  // (L + 1)^ROUNDS about 1e115
   bool done = false;
-  for (int it = 0; it < 96; ++it) {
-    // (the last term only ends the search for an exact zero)
-    if (hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin + 1e-30 * tnorm) done = true;
+  for (int it = 0; it < ROUNDS; ++it) {
+    if (hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi)) + 4.0 * pivmin) done = true;
     if (__ballot(!done) == 0ull) break;
     const double x = lo + (hi - lo) * (double)(l + 1) / (double)(L + 1);
     const int cnt = sturm_count(de, m, x, pivmin);
