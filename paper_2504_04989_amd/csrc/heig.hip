@@ -1190,7 +1190,8 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
   }
   __syncthreads();
   if (!act) return;  // (one wave, no barrier below)
-  if (nvec && t >= nvec[f]) {  // not wanted
+  // a vector that is not wanted (see heig_topk) is zero
+  if ((nvec && t >= nvec[f]) || (vfloor_rel > 0.0 && !(lam[t] > vfloor_rel * lam[0]))) {
     for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{0.0, 0.0};
     return;
   }
@@ -1213,11 +1214,9 @@ __global__ __launch_bounds__(64) void heig_invit_kernel(int m, int k, int nl, un
     res = nrm > 0.0 && isfinite(nrm) ? scale : 1.0;
     if (__ballot(!(res <= 16.0 * m * eps)) == 0ull) break;
   }
-  // eigenvalues at or below vfloor_rel * lambda_0 (when vfloor_rel > 0) get a zero vector
-  const bool floor_out = vfloor_rel > 0.0 && !(lam[t] > vfloor_rel * lam[0]);
-  if (!floor_out && !(res <= 1e3 * m * eps)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
+  if (!(res <= 1e3 * m * eps)) atomicAdd(&info[INFO_EIG_NOCONV], 1);
 #pragma unroll 4
-  for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{floor_out ? 0.0 : s.Z[i * nl] * scale, 0.0};
+  for (int i = 0; i < m; ++i) W[(int64_t)i * k] = cx<double>{s.Z[i * nl] * scale, 0.0};
 }
 
 // Orthogonalisation inside the clusters of close eigenvalues, one workgroup per
