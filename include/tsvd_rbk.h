@@ -134,7 +134,10 @@ int tsvd_version(void);
 const char* tsvd_last_error(void);
 
 /* Bytes of device workspace needed by operation `op` (TSVD_OP_*) for these
- * sizes and precision; 0 if the arguments are invalid.  Pure host function. */
+ * sizes and precision; 0 if the arguments are invalid.  Pure host function.
+ * TSVD_PREC_F32 calls with few slices also run in less, down to the scratch of
+ * fewer partial sums in the Krylov products: slower, and the same to FP32
+ * rounding instead of bit for bit. */
 size_t tsvd_workspace_bytes(int64_t n1, int64_t n2, int64_t n3, int64_t k,
                             int64_t b, int64_t q, int prec, int op);
 

@@ -147,7 +147,8 @@ int make_plan_tpinv(int64_t n1, int64_t n2, int64_t n3, int prec, Plan* p) {
   return TSVD_OK;
 }
 
-int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, Plan* p) {
+int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, bool narrow,
+                   Plan* p) {
   if (n1 < 1 || n2 < 1 || n3 < 1) return fail(TSVD_EINVAL, "n1, n2, n3 must be >= 1");
   if (op == TSVD_OP_TPINV) return make_plan_tpinv(n1, n2, n3, prec, p);
   // completion (Example 3): the approximation plan of the chosen method plus
@@ -226,13 +227,10 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
               (op == TSVD_OP_RBK || op == TSVD_OP_APPROX || op == TSVD_OP_POWER || op == TSVD_OP_POWER_APPROX ||
                ritz);
   if (p->kmode != KM_BF16) {
-    // Sizes that the entry without a workspace may take (64 MiB in all) keep
-    // the scratch of the narrow splits; the others take as many as pay: a Krylov
-    // product of 512 x 768 x 3, b = 60 (2 slices) 53 us in 2 splits, 25 in 16; 1000
-    // x 1000 x 32, b = 60 151 us in 2, 113 in 3.
-    // BF16x3 keeps them too: its products' sums stay in their order.
-    const bool narrow = p->kmode != KM_F32 ||
-                        (op == TSVD_OP_RBK && (size_t)F * n1 * n2 * 8 <= (size_t)TSVD_NOALLOC_SCRATCH_BYTES);
+    // Wide splits, as many as pay: a Krylov product of 512 x 768 x 3, b = 60 (2
+    // slices) 53 us in 2 splits, 25 in 16; 1000 x 1000 x 32, b = 60 151 us in 2, 113
+    // in 3.  BF16x3 keeps the narrow ones: its products' sums stay in their order.
+    narrow = narrow || p->kmode != KM_F32;
     p->ks_ax = p->dt == DT_F32 ? kgemm_split((int)n1, (int)n2, (int)b, (int)F, narrow) : 1;
     p->ks_ahy = p->dt == DT_F32 ? kgemm_split((int)n2, (int)n1, (int)b, (int)F, narrow) : 1;
   } else {
@@ -354,6 +352,30 @@ int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t 
   p->o_vo = take(completion ? (size_t)n2 * k * n3 * es : 0);
   p->total = o;
   return TSVD_OK;
+}
+
+// The plan of a call whose workspace has `have` bytes (all that it could use, by
+// default).  The wide K splits of the FP32 Krylov products need more scratch than
+// the narrow ones (up to twice the whole workspace, with few slices), so
+// narrow splits are taken
+//   - where the workspace holds no more, and
+//   - where the wide ones would put Alg. 2 with these sizes beyond the static
+//     scratch of tsvd_rbk_noalloc, for every operation: calls that run the same
+//     launches keep giving the same bits.
+int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, Plan* p,
+              size_t have = SIZE_MAX) {
+  int r = make_plan_with(n1, n2, n3, k, b, q, prec, op, false, p);
+  if (r || p->tensor_op || p->dt != DT_F32 || p->kmode != KM_F32) return r;
+  const int N1 = (int)n1, N2 = (int)n2, B = (int)b, F = (int)p->F;
+  if (p->ks_ax == kgemm_split(N1, N2, B, F, true) && p->ks_ahy == kgemm_split(N2, N1, B, F, true)) return r;
+  bool narrow = have < p->total;
+  const size_t lim = TSVD_NOALLOC_SCRATCH_BYTES;
+  if (!narrow && (size_t)F * n1 * n2 * 8 <= lim && b * (q + 1) <= std::min<int64_t>(1024, std::min(n1, n2))) {
+    Plan t;
+    narrow = !make_plan_with(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, false, &t) && t.total > lim &&
+             !make_plan_with(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, true, &t) && t.total <= lim;
+  }
+  return narrow ? make_plan_with(n1, n2, n3, k, b, q, prec, op, true, p) : TSVD_OK;
 }
 
 struct Ctx {
@@ -1564,7 +1586,7 @@ int svd_call(bool given, int op, const void* A, const void* Omega, uint64_t seed
              int64_t b, int64_t q, int prec, void* U, void* S, void* V, void* Xhat, void* ws, size_t ws_bytes,
              void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, k, b, q, prec, op, &p);
+  int r = make_plan(n1, n2, n3, k, b, q, prec, op, &p, ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({A, U, S, V}, ws, ws_bytes, p))) return r;
   if (given && (r = need_omega(Omega))) return r;
@@ -1586,7 +1608,8 @@ int complete_call(bool given, const void* M, const void* mask, const void* Omega
   if (alg != 1 && alg != 2) return fail(TSVD_EINVAL, "alg must be 1 (power iteration) or 2 (block Krylov)");
   if (iters < 0 || iters > 1000000) return fail(TSVD_EINVAL, "need 0 <= iters <= 1000000");
   Plan p;
-  int r = make_plan(n1, n2, n3, k, b, q, prec, alg == 2 ? TSVD_OP_COMPLETE_RBK : TSVD_OP_COMPLETE_POWER, &p);
+  int r = make_plan(n1, n2, n3, k, b, q, prec, alg == 2 ? TSVD_OP_COMPLETE_RBK : TSVD_OP_COMPLETE_POWER, &p,
+                    ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({M, C}, ws, ws_bytes, p))) return r;
   if (!mask) return fail(TSVD_EINVAL, "null mask");
@@ -1618,7 +1641,7 @@ int complete_call(bool given, const void* M, const void* mask, const void* Omega
 int proj_call(bool given, const void* A, const void* Omega, uint64_t seed, int64_t n1, int64_t n2, int64_t n3, int64_t b,
               int64_t q, int prec, void* P, void* ws, size_t ws_bytes, void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, 1, b, q, prec, TSVD_OP_PROJ, &p);
+  int r = make_plan(n1, n2, n3, 1, b, q, prec, TSVD_OP_PROJ, &p, ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({A, P}, ws, ws_bytes, p))) return r;
   if (given && (r = need_omega(Omega))) return r;
@@ -1660,7 +1683,7 @@ int proj_call(bool given, const void* A, const void* Omega, uint64_t seed, int64
 int proj_backward_call(bool given, const void* A, const void* Omega, uint64_t seed, const void* G, int64_t n1, int64_t n2,
                        int64_t n3, int64_t b, int64_t q, int prec, void* dA, void* ws, size_t ws_bytes, void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, 1, b, q, prec, TSVD_OP_PROJ_BWD, &p);
+  int r = make_plan(n1, n2, n3, 1, b, q, prec, TSVD_OP_PROJ_BWD, &p, ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({A, G, dA}, ws, ws_bytes, p))) return r;
   if (given && (r = need_omega(Omega))) return r;
@@ -1675,7 +1698,7 @@ int approx_backward_call(bool given, const void* A, const void* Omega, uint64_t 
                          int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, void* dA, void* ws,
                          size_t ws_bytes, void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_APPROX_BWD, &p);
+  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_APPROX_BWD, &p, ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({A, G, dA}, ws, ws_bytes, p))) return r;
   if (given && (r = need_omega(Omega))) return r;
@@ -1690,7 +1713,7 @@ int ritz_call(bool given, const void* A, const void* Omega, uint64_t seed, int64
               int64_t k, int64_t b, int64_t q, int prec, void* Qr, void* U, void* S, void* V, void* ws, size_t ws_bytes,
               void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK_RITZ, &p);
+  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK_RITZ, &p, ws_bytes);
   if (r) return r;
   if ((r = check_ptrs({A, Qr, U, S, V}, ws, ws_bytes, p))) return r;
   if (given && (r = need_omega(Omega))) return r;
@@ -1761,7 +1784,7 @@ int tsvd_rbk(const void* A, int64_t n1, int64_t n2, int64_t n3, int64_t k, int64
 int tsvd_rbk_noalloc(const void* A, int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q,
                      uint64_t seed, int prec, void* U, void* S, void* V, void* stream) {
   Plan p;
-  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, &p);
+  int r = make_plan(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, &p, kStaticScratchBytes);
   if (r) return r;
   if (p.total > kStaticScratchBytes) {
     char msg[160];
