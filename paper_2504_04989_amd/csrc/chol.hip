@@ -10,13 +10,13 @@
 // CholeskyQR (Fukaya et al., 2020), which keeps the factorisation defined for
 // rank-deficient or ill-conditioned blocks.
 //
-// One 256-thread workgroup per slice, threads arranged 16 x 16 over (row,
-// column) of the trailing triangle; the lower triangle lives in LDS in packed
-// row order when it fits (see chol_uses_lds) or in global scratch.
+// One 256-thread workgroup per slice.  b <= 128: one elimination with the entries in
+// registers (chol_elim.h).  Wider blocks: chol_inv_kernel, threads arranged 16 x 16
+// over (row, column) of the trailing triangle, the lower triangle in packed row
+// order in global scratch.
 #include "chol_elim.h"
 #include "common.h"
 #include "kernels.h"
-
 
 namespace tsvd {
 
@@ -25,19 +25,17 @@ __device__ __forceinline__ int tri(int i, int c) { return i * (i + 1) / 2 + c; }
 // mode 0: Gpart holds partial Gram matrices, factor G + shift I = R^H R.
 // mode 1: Gpart holds partials of an upper triangular R (its strict lower part
 //         is ignored); only the inverse is formed.
-template <bool LDS>
 __global__ __launch_bounds__(256) void chol_inv_kernel(const cx<double>* __restrict__ Gpart, int nsum,
                                                        int64_t part_stride, cx<double>* __restrict__ Rinv,
                                                        cx<double>* gscratch, int b, double shift_coef, int* info,
                                                        int mode) {
-  extern __shared__ __align__(16) unsigned char smem[];
   __shared__ cx<double> colj[1024];
   __shared__ double red[4];
   const int f = blockIdx.x;
   const int tid = threadIdx.x;
   const int tx = tid & 15, ty = tid >> 4;
   const int64_t ntri = (int64_t)b * (b + 1) / 2;
-  cx<double>* L = LDS ? reinterpret_cast<cx<double>*>(smem) : gscratch + (int64_t)f * ntri;
+  cx<double>* L = gscratch + (int64_t)f * ntri;
   const cx<double>* G = Gpart + (int64_t)f * b * b;
 
   if (mode == 1) {
@@ -161,38 +159,9 @@ __global__ __launch_bounds__(256) void chol_inv_kernel(const cx<double>* __restr
   }
 }
 
-hipError_t chol_inv_blocked(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, int b, int batch,
-                            double shift_coef, int* info, hipStream_t s, int mode);
-
-hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, void* gscratch, int b,
-                       int batch, double shift_coef, int* info, hipStream_t s, int mode) {
-  if (batch <= 0 || b <= 0) return hipSuccess;
-  if (b > 1024) return hipErrorInvalidValue;
-  if (b <= 128) return chol_inv_blocked(Gpart, nsum, part_stride, Rinv, b, batch, shift_coef, info, s, mode);
-  const size_t tri_bytes = (size_t)b * (b + 1) / 2 * sizeof(cx<double>);
-  const bool use_lds = chol_uses_lds(b);
-  static bool attr_set = false;
-  if (!attr_set) {
-    (void)hipFuncSetAttribute((const void*)chol_inv_kernel<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              140 * 1024);
-    (void)hipGetLastError();
-    attr_set = true;
-  }
-  if (use_lds)
-    hipLaunchKernelGGL(chol_inv_kernel<true>, dim3(batch), dim3(256), tri_bytes, s, (const cx<double>*)Gpart, nsum,
-                       part_stride, (cx<double>*)Rinv, nullptr, b, shift_coef, info, mode);
-  else
-    hipLaunchKernelGGL(chol_inv_kernel<false>, dim3(batch), dim3(256), 0, s, (const cx<double>*)Gpart, nsum,
-                       part_stride, (cx<double>*)Rinv, (cx<double>*)gscratch, b, shift_coef, info, mode);
-  return hipGetLastError();
-}
-
-}  // namespace tsvd
-
-// b <= 128: the elimination of chol_elim.h on the sum of the partials.
-namespace tsvd {
 namespace {
 
+// b <= 128: the elimination of chol_elim.h on the sum of the partials.
 template <int NB, int MODE>
 __global__ __launch_bounds__(256, 1) void chol_elim_kernel(const cx<double>* __restrict__ Gpart, int nsum,
                                                             int64_t part_stride, cx<double>* __restrict__ Rinv, int b,
@@ -246,12 +215,10 @@ __global__ __launch_bounds__(256, 1) void chol_elim_kernel(const cx<double>* __r
 
 }  // namespace
 
-bool chol_blocked_ok(int b) { return b <= 128; }
+bool chol_elim_ok(int64_t b) { return b <= 128; }
 
-hipError_t chol_inv_blocked(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, int b, int batch,
-                            double shift_coef, int* info, hipStream_t s, int mode) {
-  if (batch <= 0 || b <= 0) return hipSuccess;
-  if (b > 128) return hipErrorInvalidValue;
+static hipError_t chol_inv_elim(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, int b, int batch,
+                                double shift_coef, int* info, hipStream_t s, int mode) {
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3(batch), dim3(256), 0, s, (const cx<double>*)Gpart, nsum, part_stride,
                        (cx<double>*)Rinv, b, shift_coef, info);
@@ -272,6 +239,16 @@ hipError_t chol_inv_blocked(const double* Gpart, int nsum, int64_t part_stride, 
 #undef TSVD_CHOL_CASE
   }
   return hipErrorInvalidValue;
+}
+
+hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, void* gscratch, int b,
+                       int batch, double shift_coef, int* info, hipStream_t s, int mode) {
+  if (batch <= 0 || b <= 0) return hipSuccess;
+  if (b > 1024) return hipErrorInvalidValue;
+  if (chol_elim_ok(b)) return chol_inv_elim(Gpart, nsum, part_stride, Rinv, b, batch, shift_coef, info, s, mode);
+  hipLaunchKernelGGL(chol_inv_kernel, dim3(batch), dim3(256), 0, s, (const cx<double>*)Gpart, nsum, part_stride,
+                     (cx<double>*)Rinv, (cx<double>*)gscratch, b, shift_coef, info, mode);
+  return hipGetLastError();
 }
 
 }  // namespace tsvd

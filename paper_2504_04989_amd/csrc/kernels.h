@@ -111,11 +111,14 @@ hipError_t fft_r2c_split(const void* X, void* Xb, int64_t ntubes, int n3, hipStr
 // Gpart + s * part_stride complex elements, slice f at + f * b * b) -> inverse
 // of its shifted Cholesky factor R (G + shift_coef * trace(G) I = R^H R),
 // upper triangular, FP64, b x b row-major per slice.  gscratch: b(b+1)/2
-// complex doubles per slice, used when !chol_uses_lds(b).
-inline bool chol_uses_lds(int64_t b) { return b * (b + 1) / 2 * 16 <= 120 * 1024; }
+// complex doubles per slice, used unless chol_elim_ok(b).
 // mode 1: the partials sum to an upper triangular R instead; the kernel only
-// inverts it (Rinv = R^{-1}).  mode 2 (b <= 128): only the upper triangle of
+// inverts it (Rinv = R^{-1}).  mode 2 (chol_elim_ok): only the upper triangle of
 // the partials is valid; G is its Hermitian extension.
+bool chol_elim_ok(int64_t b);  // b <= 128: the elimination in registers
+hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, void* gscratch, int b,
+                       int batch, double shift_coef, int* info, hipStream_t s, int mode = 0);
+
 // Whole orthonormalisation of a small n x b block W per slice (in place if D is
 // W), one workgroup each: projection off the ib earlier columns Q, a shifted
 // CholeskyQR pass, the projection again, nshift shifted and nplain unshifted
@@ -124,9 +127,6 @@ bool orth_small_ok(int64_t n, int64_t b, int64_t ib);
 hipError_t orth_small(DType dt, const void* W, int64_t ldw, int64_t strideW, const void* Q, int64_t ldq,
                       int64_t strideQ, void* D, int64_t ldd, int64_t strideD, int n, int b, int ib, int nshift,
                       int nplain, double shift, int batch, int* info, hipStream_t s);
-bool chol_blocked_ok(int b);  // the blocked factorisation (and mode 2) applies
-hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, double* Rinv, void* gscratch, int b,
-                       int batch, double shift_coef, int* info, hipStream_t s, int mode = 0);
 
 // Per-slice m x m Hermitian PSD matrix (sum of nsum FP64 partials): top-k
 // eigenpairs.  lambda (batch x k, descending), W (batch x m x k complex FP64).

@@ -5,7 +5,7 @@
 // Bound: the chain of m steps, each a norm, a reflector, a matrix-vector
 // product, a dot product and a rank-2 update of a matrix of at most 192 x 192.
 // The arithmetic of all steps together is about 0.1 ms of one CU's FP64 rate.
-// The streaming form spent 8 to 10 us per step on its eight workgroup barriers,
+// The streaming form spent 3.5 to 10 us per step on its eight workgroup barriers,
 // LDS shuffles and the trailing matrix's round trip through L2.  Here:
 //   - the waves hold the 32 x 32 tiles of the lower triangle in registers, 4 x 4
 //     entries per lane (diagonal tiles hold both triangles, so no entry is

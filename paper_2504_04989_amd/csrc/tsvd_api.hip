@@ -285,7 +285,7 @@ int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int
   p->o_part = take(part);
   p->part_bytes = part;
   p->o_rinv = take((size_t)F * b * b * 16);
-  p->o_chol = take(chol_uses_lds(b) ? 0 : (size_t)F * b * (b + 1) / 2 * 16);
+  p->o_chol = take(chol_elim_ok(b) ? 0 : (size_t)F * b * (b + 1) / 2 * 16);
   const bool need_svd = (op == TSVD_OP_RBK || op == TSVD_OP_APPROX || power || ritz);
   const int64_t ks = ritz ? b : k;  // columns of the small SVD's buffers
   p->o_lam = take(need_svd ? (size_t)F * ks * 8 : 0);
@@ -543,7 +543,7 @@ int cholqr_pass(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t l
   double* part = c.at<double>(p.o_part);
   int nsum = 1;
   // the Gram is Hermitian: on the FP32 path (b <= 128) only its upper triangle is formed
-  const bool upper = p.dt == DT_F32 && chol_blocked_ok((int)p.b);
+  const bool upper = p.dt == DT_F32 && chol_elim_ok(p.b);
   const bool long_rows = rows == p.n1;
   int r = inner_products(c, src, lds, (int)p.b, src, lds, (int)p.b, rows, rows * lds, rows * lds,
                          long_rows ? p.nsplit_blk : p.nsplit_t, long_rows ? p.kchunk_blk : p.kchunk_t, part, &nsum,
