@@ -15,7 +15,8 @@
 // spectra are separated with X_a[f] = (Z[f] + conj Z[-f]) / 2,
 // X_b[f] = (Z[f] - conj Z[-f]) / (2i) while writing the slice-major output
 // (coalesced across tubes).  The inverse packs two Hermitian half spectra
-// the same way.  Lengths whose sequences do not fit LDS use a direct DFT.
+// the same way.  Lengths whose sequences do not fit LDS use a direct DFT, and so
+// do few tubes of a length with a prime factor above 13 (direct_pays).
 //
 // What bounds the general kernels is instruction issue and the latency of the
 // tube reads (two workgroups per CU): reads are issued eight at a time,
@@ -24,6 +25,9 @@
 // against 553 and 431 with one read at a time, hardware division and full
 // products; 160 000 tubes of 191 (prime; before, one sincos per term): 1901 and
 // 1941 us against 48244 and 7727.
+#include <algorithm>
+#include <cmath>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -330,7 +334,7 @@ __global__ __launch_bounds__(256) void fft_c2r_kernel(const cx<T>* __restrict__ 
   }
 }
 
-// Direct DFT for lengths beyond LDS: one thread per output.
+// Direct DFT: one thread per output.
 template <typename T>
 __global__ void dft_r2c_direct(const T* X, cx<T>* Xb, int64_t ntubes, int N) {
   const int F = N / 2 + 1;
@@ -376,17 +380,38 @@ static int pick_np(int N) {
   return np;
 }
 
+// Where a direct DFT beats the kernels above: lengths beyond LDS, and lengths with
+// general passes when the tubes are few.  A general pass of radix R takes NP N / 256
+// outputs of R - 1 dependent terms per thread, whatever the number of tubes, until
+// two workgroups per CU are busy; the direct form spreads its terms, each with a
+// sincos, over all CUs.  Estimates in us, fitted to 21 lengths from 17 to 1361 by 1
+// to 65536 tubes (either form within 15% of the better one, against up to 3 times
+// slower with the general passes alone: 1361 x 12 tubes, inverse 212 against 585;
+// 59 x 64 tubes 11 against 39; from 59 x 8192 tubes on, 50 against 39, and 191 x
+// 16384, 822 against 247, it is the other way round).
+static bool direct_pays(const FftPlan& p, int64_t ntubes, int NP, bool inv) {
+  int terms = 0;  // dependent terms of a thread
+  for (int s = 0; s < p.nf; ++s)
+    if (p.fac[s] > 13) terms += (NP * p.N + 255) / 256 * (p.fac[s] - 1);
+  if (terms == 0) return false;
+  const double nblk = (double)((ntubes + 2 * NP - 1) / (2 * NP));
+  const double general = (9.0 + 0.065 * terms) * std::max(1.0, nblk / 512);
+  const double work = 1e-6 * (double)ntubes * p.N * (p.N / 2 + 1);
+  const double direct = inv ? 2 + 0.27 * (p.N / 2 + 1) + 2.1 * work : std::hypot(2 + 0.28 * p.N, 3.8 * work);
+  return direct < general;
+}
+
 template <typename T>
 static hipError_t r2c_t(const void* X, void* Xb, int64_t ntubes, int n3, hipStream_t s) {
   if (ntubes <= 0) return hipSuccess;
   const int NP = pick_np<double>(n3);
-  if (NP < 1) {
+  const FftPlan plan = make_plan(n3);
+  if (NP < 1 || direct_pays(plan, ntubes, NP, false)) {
     const int64_t total = ntubes * (n3 / 2 + 1);
     hipLaunchKernelGGL(dft_r2c_direct<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, (const T*)X,
                        (cx<T>*)Xb, ntubes, n3);
     return hipGetLastError();
   }
-  const FftPlan plan = make_plan(n3);
   const int64_t nblk = (ntubes + 2 * NP - 1) / (2 * NP);
   const size_t sm = (size_t)(n3 + 2 * NP * (n3 + 1)) * sizeof(cx<double>);
   hipLaunchKernelGGL((fft_r2c_kernel<T, double>), dim3((unsigned)nblk), dim3(256), sm, s, (const T*)X, (cx<T>*)Xb,
@@ -398,13 +423,13 @@ template <typename T>
 static hipError_t c2r_t(const void* Xb, int64_t stride, void* X, int64_t ntubes, int n3, hipStream_t s) {
   if (ntubes <= 0) return hipSuccess;
   const int NP = pick_np<double>(n3);
-  if (NP < 1) {
+  const FftPlan plan = make_plan(n3);
+  if (NP < 1 || direct_pays(plan, ntubes, NP, true)) {
     const int64_t total = ntubes * n3;
     hipLaunchKernelGGL(dft_c2r_direct<T>, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s,
                        (const cx<T>*)Xb, stride, (T*)X, ntubes, n3);
     return hipGetLastError();
   }
-  const FftPlan plan = make_plan(n3);
   const int64_t nblk = (ntubes + 2 * NP - 1) / (2 * NP);
   const size_t sm = (size_t)(n3 + 2 * NP * (n3 + 1)) * sizeof(cx<double>);
   hipLaunchKernelGGL((fft_c2r_kernel<T, double>), dim3((unsigned)nblk), dim3(256), sm, s, (const cx<T>*)Xb, stride,
