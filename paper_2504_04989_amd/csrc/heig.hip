@@ -1524,6 +1524,8 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
     (void)hipFuncSetAttribute((const void*)heig_tri2_kernel<8>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               152 * 1024);
     (void)hipFuncSetAttribute((const void*)heig_tri2_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              160 * 1024 - 256);
+    (void)hipFuncSetAttribute((const void*)heig_tri2_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize,
                               152 * 1024);
     (void)hipFuncSetAttribute((const void*)heig_backxf_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
                               152 * 1024);
@@ -1545,9 +1547,13 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
         hipSuccess)
       return e;
   } else if (stages & HEIG_TRIDIAG) {
-    const int nb = sm2(8) <= lds_total ? 8 : 4;
+    // the panel's vectors in LDS: 8 reflectors up to m = 480, 4 up to 928 (all of a
+    // CU's 160 KB but the static part), 2 above
+    const int nb = sm2(8) <= lds_total ? 8 : sm2(4) <= 160 * 1024 - 256 ? 4 : 2;
     const size_t sm = sm2(nb);
-    const void* fn = nb == 8 ? (const void*)heig_tri2_kernel<8> : (const void*)heig_tri2_kernel<4>;
+    const void* fn = nb == 8   ? (const void*)heig_tri2_kernel<8>
+                     : nb == 4 ? (const void*)heig_tri2_kernel<4>
+                               : (const void*)heig_tri2_kernel<2>;
     hipLaunchKernelGGL(heig_prep_kernel, dim3(batch, PREP_WG), dim3(256), 0, s, (const cx<double>*)Gpart, nsum,
                        part_stride, m, upper_only ? 1 : 0, sc, per);
     if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1595,12 +1601,15 @@ hipError_t heig_topk(const double* Gpart, int nsum, int64_t part_stride, int m, 
       }
     }
     if (P == 1) {
+      auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(batch), dim3(T2_NT), sm, s, G, nsum_a, ps, m_a, mp_a, sc_a, per_a, up, 1, info_a);
+      };
       if (nb == 8)
-        hipLaunchKernelGGL(heig_tri2_kernel<8>, dim3(batch), dim3(T2_NT), sm, s, G, nsum_a, ps, m_a, mp_a, sc_a, per_a,
-                           up, 1, info_a);
+        go(heig_tri2_kernel<8>);
+      else if (nb == 4)
+        go(heig_tri2_kernel<4>);
       else
-        hipLaunchKernelGGL(heig_tri2_kernel<4>, dim3(batch), dim3(T2_NT), sm, s, G, nsum_a, ps, m_a, mp_a, sc_a, per_a,
-                           up, 1, info_a);
+        go(heig_tri2_kernel<2>);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
