@@ -246,7 +246,7 @@ def slice_relerr(U, S, V, sl, freqs, idx=None):
     return float(np.sqrt(num / den)), per, sig
 
 
-def run_rbk_form(api, A64, c, prec, steps, warmup, workload):
+def run_rbk_form(api, A64, c, prec, steps, warmup, workload, log_classes=False):
     """Time tsvd_rbk (seed-taking) in one precision; returns (leg, outputs)."""
     import torch
     n1, n2, n3 = A64.shape
@@ -261,7 +261,7 @@ def run_rbk_form(api, A64, c, prec, steps, warmup, workload):
     ms, kernels = time_calls(api, lambda: api.tsvd_rbk(A, seed, k, b, q, prec, ws=ws, out=out), steps, warmup)
     info = api.read_info(ws)
     log(f"[bench] {workload} {prec}: {ms:.3f} ms/step ({1e3 / ms:.2f} T-SVD/s); info {info}")
-    for cls, v in sorted(kernels.items(), key=lambda kv: -kv[1]["ms_per_step"]):
+    for cls, v in sorted(kernels.items(), key=lambda kv: -kv[1]["ms_per_step"]) if log_classes else ():
         log(f"[bench]   {cls:12s} {v['ms_per_step']:.3f} ms/step  {v['launches_per_step']:.0f} launches  "
             f"{v['avg_launch_ms'] * 1e3:.1f} us/launch")
     leg = {"value": 1e3 / ms, "ms_per_step": ms, "roofline": roofline_for(kernels, c, prec, workload),
@@ -444,6 +444,41 @@ def tqr_runs(api, inputs, steps: int, warmup: int):
     return {"workload": f"Gaussian {n1} x {n2} x {n3}, f32", "calls": res}
 
 
+def brief(res: dict) -> dict:
+    """The record on one short line: per form and workload its time, error,
+    time per kernel class and utilisation, to five digits.  (The full record
+    runs to 25 KB, which a reader that keeps the tail of the output loses.)"""
+    def form(leg):
+        out = {key: leg[key] for key in ("value", "ms_per_step", "rel_err_vs_oracle", "krylov_mfma_util",
+                                         "krylov_mfma_util_executed", "krylov_hbm_frac") if key in leg}
+        out["class_ms"] = {cls: v["ms_per_step"] for cls, v in leg["kernels"].items()}
+        out["roofline"] = {key: leg["roofline"][key] for key in ("kernel", "bound", "frac")} if leg["roofline"] else None
+        return out
+
+    def short(x):
+        if isinstance(x, dict):
+            return {key: short(v) for key, v in x.items()}
+        if isinstance(x, (list, tuple)):
+            return [short(v) for v in x]
+        return float(f"{x:.5g}") if isinstance(x, float) else x
+
+    out = {key: short(v) for key, v in res.items() if key not in ("value", "ms_per_step", "forms", "other_workloads")}
+    out = {**{key: res[key] for key in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step")}, **out}
+    if out.get("roofline"):
+        out["roofline"].pop("work")
+    out["forms"] = {p: short(form(leg)) for p, leg in res["forms"].items()}
+    if "other_workloads" in res:
+        out["other_workloads"] = {}
+        for name, w in res["other_workloads"].items():
+            if "forms" in w:
+                out["other_workloads"][name] = {p: short({key: v for key, v in form(leg).items()
+                                                          if key in ("ms_per_step", "rel_err_vs_oracle", "roofline")})
+                                                for p, leg in w["forms"].items()}
+            else:
+                out["other_workloads"][name] = short({key: v for key, v in w.items() if not isinstance(v, dict)})
+    return out
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -458,6 +493,7 @@ def main():
     ap.add_argument("--no-alg1", action="store_true", help="skip the Alg. 1 vs Alg. 2 comparison (Example 1)")
     ap.add_argument("--no-completion", action="store_true", help="skip the completion runs (Example 3)")
     ap.add_argument("--no-tqr", action="store_true", help="skip the T-QR / T-pseudoinverse timing")
+    ap.add_argument("--details", default=None, help="also write the full record (every class, slice and roofline) here")
     ap.add_argument("--calibrate-copy-mib", type=int, default=0,
                     help="only run a plain device-to-device copy of this many MiB 5 times (HBM counter calibration)")
     args = ap.parse_args()
@@ -504,7 +540,7 @@ def main():
 
     legs, outs = {}, {}
     for prec in precs:
-        legs[prec], outs[prec] = run_rbk_form(api, A64, c, prec, args.steps, args.warmup, args.workload)
+        legs[prec], outs[prec] = run_rbk_form(api, A64, c, prec, args.steps, args.warmup, args.workload, True)
     del A64
 
     others = None if args.no_legs else other_workloads(api, inputs, max(args.steps // 2, 3), 1)
@@ -576,7 +612,10 @@ def main():
         res["tqr_tpinv"] = tqr
     if base is not None:
         res["cpu_baseline"] = base
-    print(json.dumps(res), flush=True)
+    if args.details:
+        with open(args.details, "w") as fh:
+            json.dump(res, fh, indent=1)
+    print(json.dumps(brief(res)), flush=True)
 
 
 if __name__ == "__main__":
