@@ -60,9 +60,10 @@ hipError_t split_bf16x3(const void* in, void* out, int64_t n, hipStream_t s);
 // partials of the split remainder tiles (0 when there is no tail split).
 size_t kgemm_part_bytes(int M, int K, int N, int batch, int nsplit);
 // K split that gives the product enough workgroups to fill the chip: at most 8,
-// doubling while the slots are not filled and chunks keep 256 steps of K; unless
-// narrow, more (up to 16) where that shortens the makespan.
-int kgemm_split(int M, int K, int N, int batch, bool narrow);
+// doubling while the slots are not filled and chunks keep 256 steps of K, and more
+// than that, up to `most` (16 by default), where that shortens the makespan.
+constexpr int KGEMM_MOST_SPLITS = 16;
+int kgemm_split(int M, int K, int N, int batch, int most = KGEMM_MOST_SPLITS);
 // K split (at most 16) of a product with few output tiles: the count that
 // minimises rounds x (K steps per split + 6) over the device's workgroup
 // slots (two per CU), a workgroup's fixed cost taken as 6 K steps.

@@ -652,18 +652,18 @@ int64_t kgemm_tiles(int M, int N, int batch) {
 
 }  // namespace
 
-int kgemm_split(int M, int K, int N, int batch, bool narrow) {
+int kgemm_split(int M, int K, int N, int batch, int most) {
   const int64_t tiles = kgemm_tiles(M, N, batch);
   int least = 1;
   while (tiles * least < 512 && least < 8 && (int64_t)K / (2 * least) >= 256) least *= 2;
   const int kc = ((K + least - 1) / least + KSTEP - 1) / KSTEP * KSTEP;
   least = std::max((K + kc - 1) / kc, 1);
-  if (narrow || tiles >= kgemm_slots()) return least;
+  if (tiles >= kgemm_slots()) return least;
   // fewer splits than that are not taken even where they are as fast: the
   // partial sums they add up are longer, and so is their rounding error
   int best = least;
   double best_cost = split_cost(tiles, K, least) + (least > 1 ? 8 + 0.25 * least : 0);
-  for (int ns = least + 1; ns <= 16; ++ns) {
+  for (int ns = least + 1; ns <= most; ++ns) {
     // 8 steps and the partials' traffic for the reduction's launch
     const double cost = split_cost(tiles, K, ns) + 8 + 0.25 * ns;
     if (cost < best_cost) {

@@ -147,7 +147,18 @@ int make_plan_tpinv(int64_t n1, int64_t n2, int64_t n3, int prec, Plan* p) {
   return TSVD_OK;
 }
 
-int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, bool narrow,
+// Bytes of the partials of the Krylov products in ax and ahy splits (an unsplit
+// product splits its last, partial round of tiles along K).
+size_t krylov_part_bytes(const Plan& p, int ax, int ahy) {
+  const int n1 = (int)p.n1, n2 = (int)p.n2, b = (int)p.b, F = (int)p.F;
+  const bool tails = p.dt == DT_F32 && p.kmode != KM_BF16;
+  auto one = [&](int M, int K, int ns) {
+    return ns > 1 ? (size_t)ns * F * M * b * 8 : tails ? kgemm_part_bytes(M, K, b, F, 1) : 0;
+  };
+  return std::max(one(n1, n2, ax), one(n2, n1, ahy));
+}
+
+int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, int most,
                    Plan* p) {
   if (n1 < 1 || n2 < 1 || n3 < 1) return fail(TSVD_EINVAL, "n1, n2, n3 must be >= 1");
   if (op == TSVD_OP_TPINV) return make_plan_tpinv(n1, n2, n3, prec, p);
@@ -227,12 +238,12 @@ int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int
               (op == TSVD_OP_RBK || op == TSVD_OP_APPROX || op == TSVD_OP_POWER || op == TSVD_OP_POWER_APPROX ||
                ritz);
   if (p->kmode != KM_BF16) {
-    // Wide splits, as many as pay: a Krylov product of 512 x 768 x 3, b = 60 (2
-    // slices) 53 us in 2 splits, 25 in 16; 1000 x 1000 x 32, b = 60 151 us in 2, 113
-    // in 3.  BF16x3 keeps the narrow ones: its products' sums stay in their order.
-    narrow = narrow || p->kmode != KM_F32;
-    p->ks_ax = p->dt == DT_F32 ? kgemm_split((int)n1, (int)n2, (int)b, (int)F, narrow) : 1;
-    p->ks_ahy = p->dt == DT_F32 ? kgemm_split((int)n2, (int)n1, (int)b, (int)F, narrow) : 1;
+    // as many splits as pay, up to `most`: a Krylov product of 512 x 768 x 3, b = 60
+    // (2 slices) 53 us in 2 splits, 25 in 16; 1000 x 1000 x 32, b = 60 151 us in 2,
+    // 113 in 3.  BF16x3 keeps the fewest: its products' sums stay in their order.
+    if (p->kmode != KM_F32) most = 1;
+    p->ks_ax = p->dt == DT_F32 ? kgemm_split((int)n1, (int)n2, (int)b, (int)F, most) : 1;
+    p->ks_ahy = p->dt == DT_F32 ? kgemm_split((int)n2, (int)n1, (int)b, (int)F, most) : 1;
   } else {
     p->ks_ax = kgemm_bf16_split((int)n1, (int)n2, (int)b, (int)F);
     p->ks_ahy = kgemm_bf16_split((int)n2, (int)n1, (int)b, (int)F);
@@ -329,14 +340,7 @@ int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int
   p->o_zbar = take(bwd ? (size_t)F * n1 * b * cs : 0);
   p->o_tbar = take(bwd ? (size_t)F * n2 * b * cs : 0);
   {
-    size_t kp = std::max(p->ks_ax > 1 ? (size_t)p->ks_ax * F * n1 * b * 8 : 0,
-                         p->ks_ahy > 1 ? (size_t)p->ks_ahy * F * n2 * b * 8 : 0);
-    if (p->dt == DT_F32 && p->kmode != KM_BF16) {
-      // unsplit products split their last, partial round of tiles along K
-      if (p->ks_ax == 1) kp = std::max(kp, kgemm_part_bytes((int)n1, (int)n2, (int)b, (int)F, 1));
-      if (p->ks_ahy == 1) kp = std::max(kp, kgemm_part_bytes((int)n2, (int)n1, (int)b, (int)F, 1));
-    }
-    if (tensor_op) kp = 0;
+    const size_t kp = tensor_op ? 0 : krylov_part_bytes(*p, p->ks_ax, p->ks_ahy);
     p->kpart_bytes = kp;
     p->o_kpart = take(kp);
     const bool bfm = p->dt == DT_F32 && p->kmode == KM_BF16;
@@ -355,27 +359,36 @@ int make_plan_with(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int
 }
 
 // The plan of a call whose workspace has `have` bytes (all that it could use, by
-// default).  The wide K splits of the FP32 Krylov products need more scratch than
-// the narrow ones (up to twice the whole workspace, with few slices), so
-// narrow splits are taken
-//   - where the workspace holds no more, and
-//   - where the wide ones would put Alg. 2 with these sizes beyond the static
-//     scratch of tsvd_rbk_noalloc, for every operation: calls that run the same
-//     launches keep giving the same bits.
+// default).  The K splits of the FP32 Krylov products are the one part of it that
+// gives way (with few slices their partials take up to half of the workspace): their
+// number is cut
+//   - to what the workspace holds, and
+//   - so that Alg. 2 with these sizes stays within the static scratch of
+//     tsvd_rbk_noalloc where it can, for every operation: calls that run the same
+//     launches give the same bits.
+// 1000 x 1000 x 6, b = 40, q = 2: X_hat in 1396 us with all the splits that pay, 1420
+// cut to the static scratch, 1584 with the fewest.
 int make_plan(int64_t n1, int64_t n2, int64_t n3, int64_t k, int64_t b, int64_t q, int prec, int op, Plan* p,
               size_t have = SIZE_MAX) {
-  int r = make_plan_with(n1, n2, n3, k, b, q, prec, op, false, p);
+  int r = make_plan_with(n1, n2, n3, k, b, q, prec, op, KGEMM_MOST_SPLITS, p);
   if (r || p->tensor_op || p->dt != DT_F32 || p->kmode != KM_F32) return r;
-  const int N1 = (int)n1, N2 = (int)n2, B = (int)b, F = (int)p->F;
-  if (p->ks_ax == kgemm_split(N1, N2, B, F, true) && p->ks_ahy == kgemm_split(N2, N1, B, F, true)) return r;
-  bool narrow = have < p->total;
-  const size_t lim = TSVD_NOALLOC_SCRATCH_BYTES;
-  if (!narrow && (size_t)F * n1 * n2 * 8 <= lim && b * (q + 1) <= std::min<int64_t>(1024, std::min(n1, n2))) {
-    Plan t;
-    narrow = !make_plan_with(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, false, &t) && t.total > lim &&
-             !make_plan_with(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, true, &t) && t.total <= lim;
-  }
-  return narrow ? make_plan_with(n1, n2, n3, k, b, q, prec, op, true, p) : TSVD_OK;
+  int most = KGEMM_MOST_SPLITS;
+  auto ax = [&] { return kgemm_split((int)n1, (int)n2, (int)b, (int)p->F, most); };
+  auto ahy = [&] { return kgemm_split((int)n2, (int)n1, (int)b, (int)p->F, most); };
+  // lowers `most` until the plan with the other splits stays within lim bytes (or
+  // the splits are the fewest)
+  auto cut = [&](const Plan& plan, size_t lim) {
+    const size_t rest = plan.total - align256(plan.kpart_bytes);
+    while (most > 1 && rest + align256(krylov_part_bytes(plan, ax(), ahy())) > lim) --most;
+  };
+  Plan t;
+  if ((size_t)p->F * n1 * n2 * 8 <= (size_t)TSVD_NOALLOC_SCRATCH_BYTES &&
+      b * (q + 1) <= std::min<int64_t>(1024, std::min(n1, n2)) &&
+      !make_plan_with(n1, n2, n3, k, b, q, prec, TSVD_OP_RBK, 1, &t) && t.total <= TSVD_NOALLOC_SCRATCH_BYTES)
+    cut(t, TSVD_NOALLOC_SCRATCH_BYTES);
+  cut(*p, have);
+  if (ax() == p->ks_ax && ahy() == p->ks_ahy) return TSVD_OK;
+  return make_plan_with(n1, n2, n3, k, b, q, prec, op, most, p);
 }
 
 struct Ctx {
@@ -1305,7 +1318,7 @@ int slice_gemm(const Ctx& c, const void* B, bool herm, const void* X, int64_t ld
   k.batch = F;
   k.mode = KM_F32;
   k.acc = add ? 1 : 0;
-  k.nsplit = kgemm_split(M, K, N, F, false);
+  k.nsplit = kgemm_split(M, K, N, F);
   if (k.nsplit > 1 && kgemm_part_bytes(M, K, N, F, k.nsplit) > part_bytes) k.nsplit = 1;
   k.part = part;
   k.part_bytes = part_bytes;
