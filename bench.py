@@ -81,10 +81,11 @@ def class_work(cls: str, c: dict, prec: str):
         # On FP32 storage the first projection pass (coefficients and update,
         # 16 n1 (i b) b flops against block i) runs in FP32 arithmetic on the
         # FP32 MFMA, the rest in FP64: the peak is the rate at which the mix
-        # would run with every part at its own published peak.
+        # would run with every part at its own published peak.  FP64 blocks are
+        # projected three times.
         passes = 5 if prec == "f64" else cholqr_passes(n1, b)
         proj = sum(16.0 * n1 * (i * b) * b for i in range(1, q + 1))
-        fl = 2 * proj + (q + 1) * passes * 8.0 * n1 * b * (b + 1)
+        fl = (3 if prec == "f64" else 2) * proj + (q + 1) * passes * 8.0 * n1 * b * (b + 1)
         fl32 = 0.0 if prec == "f64" else proj
         p64, p32 = PEAK["mfma_tflops"]["f64"] * 1e12, PEAK["mfma_tflops"]["f32"] * 1e12
         peak = fl / ((fl - fl32) / p64 + fl32 / p32)

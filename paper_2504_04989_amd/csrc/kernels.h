@@ -121,13 +121,14 @@ hipError_t chol_inv_ex(const double* Gpart, int nsum, int64_t part_stride, doubl
                        int batch, double shift_coef, int* info, hipStream_t s, int mode = 0);
 
 // Whole orthonormalisation of a small n x b block W per slice (in place if D is
-// W), one workgroup each: projection off the ib earlier columns Q, a shifted
-// CholeskyQR pass, the projection again, nshift shifted and nplain unshifted
-// passes.  orth_small_ok: the block fits (b <= 32, W and the coefficients in LDS).
+// W), one workgroup each: projection off the ib earlier columns Q, nshift shifted
+// CholeskyQR passes, the projection again, nplain unshifted passes, with a third
+// projection after the first of them on request.
+// orth_small_ok: the block fits (b <= 32, W and the coefficients in LDS).
 bool orth_small_ok(int64_t n, int64_t b, int64_t ib);
 hipError_t orth_small(DType dt, const void* W, int64_t ldw, int64_t strideW, const void* Q, int64_t ldq,
                       int64_t strideQ, void* D, int64_t ldd, int64_t strideD, int n, int b, int ib, int nshift,
-                      int nplain, double shift, int batch, int* info, hipStream_t s);
+                      int nplain, bool third, double shift, int batch, int* info, hipStream_t s);
 
 // Per-slice m x m Hermitian PSD matrix (sum of nsum FP64 partials): top-k
 // eigenpairs.  lambda (batch x k, descending), W (batch x m x k complex FP64).

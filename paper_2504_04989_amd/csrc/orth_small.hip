@@ -29,7 +29,8 @@ struct OrthArgs {
   void* D;        // result, n x b (may be W)
   int64_t ldd, strideD;
   int n, b, ib;
-  int nshift, nplain;  // shifted and unshifted passes after the second projection
+  int nshift, nplain;  // shifted passes before the second projection, unshifted ones after it
+  bool third;          // projected once more after the first unshifted pass
   double shift;        // shift coefficient of the shifted passes
   int* info;
 };
@@ -208,10 +209,12 @@ __global__ __launch_bounds__(256, 1) void orth_small_kernel(const OrthArgs a) {
   };
 
   if (ib > 0) project();
-  pass(a.shift);
-  if (ib > 0) project();
   for (int i = 0; i < a.nshift; ++i) pass(a.shift);
-  for (int i = 0; i < a.nplain; ++i) pass(0.0);
+  if (ib > 0) project();
+  for (int i = 0; i < a.nplain; ++i) {
+    if (i > 0 && a.third) project();
+    pass(0.0);
+  }
 
   cx<T>* D = static_cast<cx<T>*>(a.D) + (int64_t)f * a.strideD;
   for (int e = tid; e < n * b; e += 256) {
@@ -251,10 +254,10 @@ bool orth_small_ok(int64_t n, int64_t b, int64_t ib) {
 
 hipError_t orth_small(DType dt, const void* W, int64_t ldw, int64_t strideW, const void* Q, int64_t ldq,
                       int64_t strideQ, void* D, int64_t ldd, int64_t strideD, int n, int b, int ib, int nshift,
-                      int nplain, double shift, int batch, int* info, hipStream_t s) {
+                      int nplain, bool third, double shift, int batch, int* info, hipStream_t s) {
   if (n <= 0 || b <= 0 || batch <= 0) return hipSuccess;
   if (!orth_small_ok(n, b, ib)) return hipErrorInvalidValue;
-  const OrthArgs a{W, ldw, strideW, Q, ldq, strideQ, D, ldd, strideD, n, b, ib, nshift, nplain, shift, info};
+  const OrthArgs a{W, ldw, strideW, Q, ldq, strideQ, D, ldd, strideD, n, b, ib, nshift, nplain, third, shift, info};
   if (dt == DT_F64) return b <= 16 ? launch<double, 1>(a, batch, s) : launch<double, 2>(a, batch, s);
   return b <= 16 ? launch<float, 1>(a, batch, s) : launch<float, 2>(a, batch, s);
 }

@@ -702,55 +702,82 @@ bool one_plain_pass(int64_t rows, int64_t b) {
   return alpha_max * u64 * 1e16 <= 0x1p-20;
 }
 
-// Shifted CholeskyQR3 of a rows x b block whose first pass has been done
-// (result in S1): dst = orthonormal basis of its range.
-int cholqr_finish(const Ctx& c, int64_t rows, void* dst, int64_t ldd) {
+// Shifted CholeskyQR passes of a rows x b block (row stride lds), result in S1.
+int cholqr_shifted(const Ctx& c, const void* src, int64_t lds, int64_t rows) {
   const Plan& p = c.p;
   void* S0 = c.at(p.o_s0);
   void* S1 = c.at(p.o_s1);
   int r;
-  if (p.dt == DT_F64) {
-    // FP64 blocks can be far more ill-conditioned than FP32 ones, whose
-    // rounding noise bounds the condition number near 1e8: a slice spectrum
-    // that reaches the FP64 rounding level within one block gives
-    // kappa >= 1/u.  One shifted pass then leaves kappa above u^{-1/2}
-    // (rounding in W R^{-1}); two more bring it down before the unshifted
-    // CholeskyQR2.
-    if ((r = cholqr_pass(c, S1, p.b, S0, p.b, true, rows))) return r;
-    if ((r = cholqr_pass(c, S0, p.b, S1, p.b, true, rows))) return r;
-    if ((r = cholqr_pass(c, S1, p.b, S0, p.b, false, rows))) return r;
-    return cholqr_pass(c, S0, p.b, dst, ldd, false, rows);
-  }
-  if (one_plain_pass(rows, p.b)) return cholqr_pass(c, S1, p.b, dst, ldd, false, rows);
+  if ((r = cholqr_pass(c, src, lds, S1, p.b, true, rows))) return r;
+  if (p.dt != DT_F64) return TSVD_OK;
+  // FP64 blocks can be far more ill-conditioned than FP32 ones, whose
+  // rounding noise bounds the condition number near 1e8: a slice spectrum
+  // that reaches the FP64 rounding level within one block gives
+  // kappa >= 1/u.  One shifted pass then leaves kappa above u^{-1/2}
+  // (rounding in W R^{-1}); two more bring it down before the unshifted
+  // CholeskyQR2.
+  if ((r = cholqr_pass(c, S1, p.b, S0, p.b, true, rows))) return r;
+  return cholqr_pass(c, S0, p.b, S1, p.b, true, rows);
+}
+
+// The unshifted passes of the block in S1: dst = orthonormal basis of its range.
+// again > 0: two, with another projection off Q_<again between them.
+int cholqr_plain(const Ctx& c, int64_t rows, void* dst, int64_t ldd, int again = 0) {
+  const Plan& p = c.p;
+  void* S0 = c.at(p.o_s0);
+  void* S1 = c.at(p.o_s1);
+  int r;
+  if (!again && p.dt != DT_F64 && one_plain_pass(rows, p.b)) return cholqr_pass(c, S1, p.b, dst, ldd, false, rows);
   if ((r = cholqr_pass(c, S1, p.b, S0, p.b, false, rows))) return r;
+  if ((r = project_out(c, S0, again))) return r;
   return cholqr_pass(c, S0, p.b, dst, ldd, false, rows);
 }
+
+// Whether block i is projected a third time.  Where A_f has a lower rank than Q_<i
+// has columns, all that the first projection leaves of a column is rounding noise,
+// with a part within Q_<i at least as large as the one outside.  The shifted passes
+// raise it to full length, so the second projection stands after the last of them.
+// What that one leaves within Q_<i is the orthogonality error of Q_<i over the
+// length that it leaves of the columns: the error grows from block to block, by
+// more in each.  A third projection, of columns made orthonormal in between, ends
+// that.  FP64 blocks always get it.  FP32 ones get it where the error would leave
+// the FP32 rounding: after four blocks of the recursion (260 noiseless tensors of
+// random sizes, max ||P(A) - A|| / ||A|| at q <= 3 2e-6, at q = 4 2e-5, from q = 5
+// on 1 without), after two panels of the T-QR, whose columns are all of one matrix.
+// Max |Q^H Q - I| with only two projections, the second after the first shifted
+// pass, against now: 161 x 120 slices of rank 30, b = 17, q = 3 FP64 0.6 against
+// 4e-15; T-QR of 1000 x 1000 of rank 10 FP64 1 against 3e-15, FP32 1 against 6e-8.
+// Cost, whole calls of Alg. 2 FP64 with the approximation: 64 x 64 x 16, b = 10, q = 2
+// 437 against 442 us, 256^3, b = 50, q = 2 5404 against 5499.
+bool third_projection(const Plan& p, int64_t i, bool panels) { return i >= (p.dt == DT_F64 ? 1 : panels ? 2 : 4); }
 
 // A block that one workgroup per slice orthonormalises whole.
 int orth_small_block(const Ctx& c, const void* src, int64_t lds, void* dst, int64_t ldd, int64_t rows, int ib) {
   const Plan& p = c.p;
   const bool f64 = p.dt == DT_F64;
+  const bool third = third_projection(p, ib / p.b, false);
   Timed tm_(K_GEMM_ORTH, c.s);
   HIPCHK(orth_small(p.dt, src, lds, rows * lds, c.at(p.o_q), p.m, p.n1 * p.m, dst, ldd, rows * ldd, (int)rows,
-                    (int)p.b, ib, f64 ? 2 : 0, f64 ? 2 : one_plain_pass(rows, p.b) ? 1 : 2, cholqr_shift(rows, p.b),
-                    (int)p.F, c.info(), c.s));
+                    (int)p.b, ib, f64 ? 3 : 1, f64 || third || !one_plain_pass(rows, p.b) ? 2 : 1, third,
+                    cholqr_shift(rows, p.b), (int)p.F, c.info(), c.s));
   return TSVD_OK;
 }
 
 // Orthonormalise the block in S0 against Q_<i and write it to Q(:, i b : (i+1) b).
 // first32: the first projection pass in FP32 arithmetic (FP32 blocks of the
 // stabilised recursion, whose blocks are orthonormalised one by one).
-int orth_block(const Ctx& c, int i, bool first32 = false) {
+// panels: the blocks are the columns of one matrix (more than 64 a panel if there
+// are two, so none of FP32 goes to orth_small_block).
+int orth_block(const Ctx& c, int i, bool first32 = false, bool panels = false) {
   const Plan& p = c.p;
   void* S0 = c.at(p.o_s0);
-  void* S1 = c.at(p.o_s1);
   void* dst = c.at<unsigned char>(p.o_q) + (size_t)i * p.b * p.cs;
   int r;
   if (orth_small_ok(p.n1, p.b, i * p.b)) return orth_small_block(c, S0, p.b, dst, p.m, p.n1, (int)(i * p.b));
   if ((r = (first32 && p.dt == DT_F32) ? project_out_f32(c, S0, i) : project_out(c, S0, i))) return r;
-  if ((r = cholqr_pass(c, S0, p.b, S1, p.b, true, p.n1))) return r;
-  if ((r = project_out(c, S1, i))) return r;
-  return cholqr_finish(c, p.n1, dst, p.m);
+  if ((r = cholqr_shifted(c, S0, p.b, p.n1))) return r;
+  if ((r = project_out(c, c.at(p.o_s1), i))) return r;
+  return cholqr_plain(c, p.n1, dst, p.m, third_projection(p, i, panels) ? i : 0);
 }
 
 // Orthonormalise an n2 x b block in place (ld b): Alg. 1's half-step iterate.
@@ -758,8 +785,8 @@ int orth_rows_n2(const Ctx& c, void* X) {
   const Plan& p = c.p;
   int r;
   if (orth_small_ok(p.n2, p.b, 0)) return orth_small_block(c, X, p.b, X, p.b, p.n2, 0);
-  if ((r = cholqr_pass(c, X, p.b, c.at(p.o_s1), p.b, true, p.n2))) return r;
-  return cholqr_finish(c, p.n2, X, p.b);
+  if ((r = cholqr_shifted(c, X, p.b, p.n2))) return r;
+  return cholqr_plain(c, p.n2, X, p.b);
 }
 
 // Out (M x N, ld ldc) = A_f (n1 x n2) * X (n2 x N, ld ldx): the big products.
@@ -1244,7 +1271,7 @@ int tqr_core(const Ctx& c, const void* A, int* nsum) {
                               c.at<unsigned char>(p.o_abar) + (size_t)i * p.b * p.cs, (size_t)p.n2 * p.cs,
                               (size_t)p.b * p.cs, (size_t)(p.F * p.n1), hipMemcpyDeviceToDevice, c.s));
     }
-    if ((r = orth_block(c, i))) return r;
+    if ((r = orth_block(c, i, false, true))) return r;
   }
   return inner_products(c, c.at(p.o_q), p.m, (int)p.m, c.at(p.o_abar), p.n2, (int)p.n2, p.n1, p.n1 * p.m,
                         p.n1 * p.n2, p.nsplit_r, p.kchunk_r, c.at<double>(p.o_part), nsum, K_GEMM_ORTH, true);
