@@ -6,7 +6,7 @@
 // factorisations it is 15 to 19 launches of 4 to 14 us each, of which the
 // arithmetic is a fraction of a microsecond.  Here a pass costs its barriers,
 // the b steps of the elimination and a few dozen dependent MFMAs: 64
-// x 10 FP64 blocks (five passes, 9 slices) 40 us each against about 170, 150 x 9
+// x 10 FP64 blocks (five passes, 9 slices) 42 us each against about 170, 150 x 9
 // FP32 blocks 37 against about 110.
 //
 // Products (v_mfma_f64_16x16x4, 16 x 16 tiles): coefficients Q^H W and Grams
